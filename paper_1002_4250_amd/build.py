@@ -51,8 +51,8 @@ def instances():
 
 
 KERNEL_DEPS = ["tsqr_inst.hip", "tsqr_device.h", "tsqr_mixed.h", "tsqr_q.h", "tsqr_internal.h", "tsqr_instances.h",
-               "tsqr_mlp.h"]
-API_DEPS = ["tsqr_api.cpp", "tsqr_internal.h", "tsqr_instances.h", "tsqr_mixed.h", "tsqr_device.h"]
+               "tsqr_mlp.h", "tsqr_panel.h"]
+API_DEPS = ["tsqr_api.cpp", "tsqr_internal.h", "tsqr_instances.h", "tsqr_mixed.h", "tsqr_device.h", "tsqr_panel.h"]
 
 
 def _digest(names):

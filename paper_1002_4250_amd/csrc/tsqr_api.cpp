@@ -265,8 +265,9 @@ int geqr_r(tsqr_handle_t h, int64_t m, int64_t n, const T* A, int64_t lda, T* R,
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the tree counters are zeroed by a kernel on every call: their position
     // depends on the leaf count, so a previous call with another leaf count may
-    // have left triangle data there
-    hipError_t e = tsqr::launch_zero_u32(a.tickets, a.leaves, s);
+    // have left triangle data there.  Up to four leaves meet inside one
+    // workgroup and use no counter, which saves the launch.
+    hipError_t e = a.leaves > 4 ? tsqr::launch_zero_u32(a.tickets, a.leaves, s) : hipSuccess;
     if (e == hipSuccess) e = dispatch_leaf<T>(a, g.nc, g.rpl, s);
     return hip_status(h, e);
 }
@@ -707,7 +708,8 @@ int batch_exec(tsqr_batch_plan_t plan, const void* A, void* R, int64_t ldr, void
     if (plan->h->planning_only) return TSQR_ERR_NO_DEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned* tickets = static_cast<unsigned*>(ws);
-    hipError_t e = tsqr::launch_zero_u32(tickets, plan->leaves, s);
+    // an instance of one leaf has no tree and uses no counter
+    hipError_t e = plan->leaves > plan->batch ? tsqr::launch_zero_u32(tickets, plan->leaves, s) : hipSuccess;
     if (e != hipSuccess) return hip_status(plan->h, e);
     if (plan->dtype == TSQR_F64) {
         tsqr::BatchArgs<double> a;

@@ -123,6 +123,12 @@ __device__ __forceinline__ double fmadd(double a, double b, double c) { return _
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double absv(double x) { return __builtin_fabs(x); }
 __device__ __forceinline__ float absv(float x) { return __builtin_fabsf(x); }
+__device__ __forceinline__ double maxv(double a, double b) { return __builtin_fmax(a, b); }
+__device__ __forceinline__ float maxv(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ double minv(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ float minv(float a, float b) { return __builtin_fminf(a, b); }
+__device__ __forceinline__ double copysignv(double a, double b) { return __builtin_copysign(a, b); }
+__device__ __forceinline__ float copysignv(float a, float b) { return __builtin_copysignf(a, b); }
 
 // Value of x held by the lane whose byte address (4 * lane) is src.
 __device__ __forceinline__ double bpermute(int src, double x)
@@ -148,19 +154,22 @@ __device__ __forceinline__ float lane_value(float x, int l)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
-__device__ __forceinline__ void wave_sync() { __syncthreads(); }
+// This thread's lane in its wavefront (workgroups may hold several)
+__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
 // Orders this wavefront's LDS accesses around a point without constraining
 // arithmetic: LDS operations of one wavefront execute in order, so only the
 // compiler has to be kept from moving them across.
-// This thread's lane in its wavefront (workgroups may hold several)
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
-
 __device__ __forceinline__ void lds_order()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// Makes what this wavefront's lanes wrote to LDS visible to its other lanes.
+// A wavefront's LDS operations execute in order, so this needs no barrier
+// instruction, and the wavefronts of a workgroup need not reach it together.
+__device__ __forceinline__ void wave_sync() { lds_order(); }
 
 // ---- reflector scalars ---------------------------------------------------------
 
@@ -212,19 +221,19 @@ __device__ __forceinline__ Reflector<T> make_reflector(T alpha, T sigma2)
 // ---- one Householder step of a leaf -------------------------------------------
 
 // Where a leaf prefetches its next chunk from.  A register slot holds four
-// columns (one per lane row); once its four columns are finished (after step
-// 4s+3) the whole slot is refilled with the next chunk's columns 4s..4s+3 by
-// one wavefront-wide load per register, into registers no later step of the
-// current chunk reads, so no step waits for the loads.  `col` is a per-lane
-// running pointer to (row base + p, column 4s + q) of the next slot; lda and n
-// pass through an opaque register copy so the compiler keeps that one pointer
-// instead of precomputing one address per slot.
+// columns; once they are finished (after panel s) the whole slot is refilled
+// with the next chunk's columns 4s..4s+3 by one wavefront-wide load per
+// register, into registers no later panel of the current chunk reads, so no
+// panel waits for the loads.  `col` is a per-lane running pointer to (row base
+// + p, column 4s + q) of the next slot; lda and n pass through an opaque
+// register copy so the compiler keeps that one pointer instead of precomputing
+// one address per slot.
 //
-// The loads are branch-free: a lane whose column lies past n reads from a
-// block of zeros instead, so in a chunk whose rows all lie inside the leaf
-// (every chunk but a ragged last one) each register is one load at a constant
-// offset.  Only a ragged chunk selects per row.  `state` is uniform: 0 no next
-// chunk, 1 full chunk, 2 ragged chunk.
+// Only a chunk whose rows all lie inside the leaf is prefetched, and the loads
+// are branch-free (a lane whose column lies past n reads from a block of zeros
+// instead), so that the number of loads in flight is known at compile time: with
+// a branch around them the compiler waits for all of them at the top of the
+// chunk loop, the last panel's included, a full memory latency per chunk.
 static __device__ double kZerosF64[256];
 static __device__ float kZerosF32[256];
 __device__ __forceinline__ const double* zeros_for(const double*) { return kZerosF64; }
@@ -236,46 +245,32 @@ struct Prefetch {
     const TIn* zero;     // per lane: zero block + p
     int64_t lda4;        // uniform: 4 * lda
     int cols_left;       // per lane: n - (4s + q)
-    int state;           // uniform: 0 none, 1 full chunk, 2 ragged chunk
-    int rows;            // uniform: rows of the next chunk inside the leaf
 };
 
 template <typename T, int RPL, typename TIn = T>
-__device__ __forceinline__ Prefetch<T, RPL, TIn> make_prefetch(const TIn* A, int64_t lda, int n, int64_t base,
-                                                               int64_t r1, int q, int p)
+__device__ __forceinline__ Prefetch<T, RPL, TIn> make_prefetch(const TIn* A, int64_t lda, int n, int64_t base, int q,
+                                                               int p)
 {
     static_assert(16 * RPL <= 256, "zero block too small");
     Prefetch<T, RPL, TIn> pf;
-    int64_t ld = lda;
-    int nn = n;
-    asm volatile("" : "+s"(ld), "+s"(nn));
-    pf.col = A + (base < r1 ? base : 0) + p + (int64_t)q * ld;
+    int ldlo = __builtin_amdgcn_readfirstlane((int)lda), ldhi = __builtin_amdgcn_readfirstlane((int)(lda >> 32));
+    int nn = __builtin_amdgcn_readfirstlane(n);
+    asm volatile("" : "+s"(ldlo), "+s"(ldhi), "+s"(nn));
+    const int64_t ld = (int64_t)(((uint64_t)(uint32_t)ldhi << 32) | (uint32_t)ldlo);
+    pf.col = A + base + p + (int64_t)q * ld;
     pf.zero = zeros_for(A) + p;
     pf.lda4 = 4 * ld;
     pf.cols_left = nn - q;
-    const int64_t left = r1 - base;
-    pf.state = left <= 0 ? 0 : (left >= 16 * RPL ? 1 : 2);
-    pf.rows = left <= 0 ? 0 : (left >= 16 * RPL ? 16 * RPL : (int)left);
     return pf;
 }
 
 // Fill register slot `slot` with the next chunk's columns and advance.
-template <typename T, int RPL, int NS, typename TIn>
-__device__ __forceinline__ void prefetch_slot(T (&c)[RPL][NS], int slot, Prefetch<T, RPL, TIn>& pf, int p)
+template <typename T, int RPL, typename TIn, typename C>
+__device__ __forceinline__ void prefetch_slot(C& c, int slot, Prefetch<T, RPL, TIn>& pf)
 {
-    if (pf.state != 0) {
-        const TIn* ptr = pf.cols_left > 0 ? pf.col : pf.zero;
-        if (pf.state == 1) {
+    const TIn* ptr = pf.cols_left > 0 ? pf.col : pf.zero;
 #pragma unroll
-            for (int r = 0; r < RPL; ++r) c[r][slot] = (T)ptr[16 * r];
-        } else {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const bool ok = p + 16 * r < pf.rows;
-                c[r][slot] = (T)*(ok ? ptr + 16 * r : pf.zero + 16 * r);
-            }
-        }
-    }
+    for (int r = 0; r < RPL; ++r) c.put(r, slot, (T)ptr[16 * r]);
     pf.col += pf.lda4;
     pf.cols_left -= 4;
 }
@@ -292,118 +287,6 @@ struct VSink {
     int64_t cbase;    // first row of the chunk
     int n;
 };
-
-// Step J of R := qr([R; C]) with R packed in LDS (Rs) and C in registers.  The
-// NC steps of a chunk are unrolled at compile time so every register index is
-// static and the scheduler can overlap consecutive steps.
-template <typename T, int NC, int RPL, int J, bool WQ, typename TIn>
-__device__ __forceinline__ void hh_step(T (&c)[RPL][Slots<NC>::NS], T* Rs, T* red, int q, int p,
-                                        int kcol, int spare, Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
-{
-    constexpr int NS = Slots<NC>::NS;
-    constexpr int QJ = J % 4, SJ = J / 4;     // lane row and slot holding column J
-    constexpr int K = NC - 1 - J;             // trailing columns
-    constexpr int OFF = Tri<NC>::off(J);
-
-    // R(J, J) and, for the lane that completes column k, R(J, k): row J of R
-    // last changed at step J of the previous chunk, so both reads are issued
-    // first and are long complete when needed.  Lanes that own no trailing
-    // column read and later write a spare LDS cell, keeping the step free of
-    // branches.
-    const int k = kcol;
-    const bool own = (k > J) && (k < NC);
-    const int ridx = own ? OFF + k - J : spare;
-    const T alpha = Rs[OFF];
-    const T rjk = Rs[ridx];
-
-    // (a) the pivot column in every lane row
-    const int src = ((QJ << 4) | p) << 2;
-    T x[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) x[r] = bpermute(src, c[r][SJ]);
-
-    // (b) partial dot products of the live slots (slot SJ is live only in
-    // lane rows q > QJ; elsewhere its result is ignored), one 16 x 17 LDS tile
-    // per lane row: writer p puts slot s at [s][p].  They are issued before
-    // the reflector so that its dependent chain runs under the LDS round trip.
-    T* rq = red + q * 16 * kRedStride;
-    if constexpr (K > 0) {
-        static_for<SJ, NS>([&](auto sc) {
-            constexpr int s = decltype(sc)::value;
-            T acc = x[0] * c[0][s];
-#pragma unroll
-            for (int r = 1; r < RPL; ++r) acc = fmadd(x[r], c[r][s], acc);
-            rq[s * kRedStride + p] = acc;
-        });
-    }
-    lds_order();
-    // (c) lane (q, p) gathers the 16 partials of column k = 4p + q
-    T u[16];
-    T fown = T(0);
-    if constexpr (K > 0) {
-        const T* rd = rq + p * kRedStride;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) u[i] = rd[i];
-    }
-
-    // the norm of the pivot column and its reflector
-    T sp = x[0] * x[0];
-#pragma unroll
-    for (int r = 1; r < RPL; ++r) sp = fmadd(x[r], x[r], sp);
-    const T sigma2 = row_allreduce16(sp);
-    const Reflector<T> h = make_reflector(alpha, sigma2);
-    if constexpr (WQ) {
-        if (q == 0 && J < vs.n) {
-            T* col = vs.V + vs.cbase + p + (int64_t)J * vs.ldv;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) col[16 * r] = h.s * x[r];
-        }
-        if (q == 0 && p == 0) vs.tau[J] = h.tau;
-    }
-
-    if constexpr (K > 0) {
-#pragma unroll
-        for (int hh = 8; hh >= 1; hh >>= 1)
-#pragma unroll
-            for (int i = 0; i < hh; ++i) u[i] = u[i] + u[i + hh];
-        const T w = fmadd(h.s, u[0], rjk);
-        Rs[ridx] = fmadd(-h.tau, w, rjk);
-        fown = own ? h.ts * w : T(0);
-    }
-    if (q == 0 && p == 0) Rs[OFF] = h.beta;
-    lds_order();
-
-    if constexpr (K > 0) {
-        // (d) rank-1 update of the live slots; the coefficient of slot s (column
-        // 4s + q) is held by lane s of the lane row and reaches the other 15
-        // lanes by a row broadcast (DPP row_newbcast), not through LDS
-        static_for<SJ, NS>([&](auto sc) {
-            constexpr int s = decltype(sc)::value;
-            const T f = dpp_mov<0x150 + s>(fown);
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) c[r][s] = fmadd(-f, x[r], c[r][s]);
-        });
-    }
-
-    // (e) slot SJ is finished in every lane row once its last column is the
-    // pivot: it takes the next chunk's columns
-    if constexpr (QJ == 3 || J == NC - 1) prefetch_slot<T, RPL, NS, TIn>(c, SJ, pf, p);
-}
-
-template <typename T, int NC, int RPL, bool WQ, typename TIn>
-__device__ __forceinline__ void merge_chunk(T (&c)[RPL][Slots<NC>::NS], T* Rs, T* red, int q, int p,
-                                            Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
-{
-    // the column a lane completes in the reduction, passed through an opaque
-    // copy so the compiler does not precompute (and keep live) one
-    // ownership predicate per step
-    int kcol = 4 * p + q;
-    asm volatile("" : "+v"(kcol));
-    const int spare = Tri<NC>::kSize;      // one LDS cell past the triangle
-    static_for<0, NC>([&](auto jc) {
-        hh_step<T, NC, RPL, decltype(jc)::value, WQ, TIn>(c, Rs, red, q, p, kcol, spare, pf, vs);
-    });
-}
 
 // ---- the operator with one column per lane -------------------------------------
 //
@@ -499,7 +382,35 @@ __device__ __forceinline__ void triangle_to_lds(const T* __restrict__ src, T* ds
     }
 }
 
+}  // namespace dev
+}  // namespace tsqr
+
+#include "tsqr_panel.h"
+
+namespace tsqr {
+namespace dev {
+
 // ---- the fused leaf + tree kernel --------------------------------------------
+
+// One chunk of a leaf: the panels in order, each followed (with PF) by the
+// loads of the next chunk's columns into its registers, which no later panel
+// reads.
+template <typename T, int NC, int RPL, bool WQ, bool PF, typename TIn>
+__device__ __forceinline__ void leaf_chunk(Chunk<T, RPL, Slots<NC>::NS>& c, T* Rs, T* work, int q, int p,
+                                           Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
+{
+    static_for<0, Slots<NC>::NS>([&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        panel_step<T, NC, RPL, RPL, P, WQ>(
+            c, Rs, work, [&](int rb, T v, const T(&tau)[4], int lo, int hi) {
+                const int k = 4 * P + q;
+                if (k < vs.n && q >= lo && q < hi) vs.V[vs.cbase + 16 * rb + p + (int64_t)k * vs.ldv] = v;
+                if (rb == 0 && lane_id() == 0)
+                    for (int j = lo; j < hi; ++j) vs.tau[4 * P + j] = tau[j];
+            });
+        if constexpr (PF) prefetch_slot<T, RPL, TIn>(c, P, pf);
+    });
+}
 
 // One leaf of one instance, then that instance's reduction tree: the body
 // shared by the single-matrix kernel and the batched kernel.  `a` describes the
@@ -519,7 +430,9 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
     constexpr int NT = Tri<NC>::kSize;
     constexpr int NS = Slots<NC>::NS;
     const int lane = lane_id();
-    const int q = lane >> 4, p = lane & 15;
+    // column 4s + q and row p + 16 r of register (r, s)
+    using C = Chunk<T, RPL, NS>;
+    const int q = C::q(lane), p = C::p(lane);
     const int64_t r0 = (int64_t)leaf * a.leaf_rows;
     const int64_t r1 = (r0 + a.leaf_rows < a.m) ? r0 + a.leaf_rows : a.m;
     const uint64_t t_start = a.stamps ? (uint64_t)wall_clock64() : 0;
@@ -528,24 +441,11 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
 
     // step 1 of the method: the local factorisation of rows [r0, r1)
     if (r1 > r0) {
-        T c[RPL][NS];
-        {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int64_t row = r0 + p + 16 * r;
-                const bool ok = row < r1;
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int k = 4 * s + q;
-                    c[r][s] = (ok && k < a.n) ? (T)a.A[row + (int64_t)k * a.lda] : T(0);
-                }
-            }
-        }
+        C c;
         wave_sync();
-        const int64_t nchunks = (r1 - r0 + CH - 1) / CH;
-        for (int64_t t = 0; t < nchunks; ++t) {
-            Prefetch<T, RPL, TIn> pf = make_prefetch<T, RPL, TIn>(a.A, a.lda, a.n, r0 + (t + 1) * CH, r1, q, p);
-            VSink<T> vs{};
+        const int64_t nfull = (r1 - r0) / CH, nchunks = (r1 - r0 + CH - 1) / CH;
+        VSink<T> vs{};
+        auto sink = [&](int64_t t) {
             if constexpr (WQ) {
                 vs.V = a.qs.V;
                 vs.ldv = a.qs.ldv;
@@ -553,7 +453,29 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
                 vs.n = a.n;
                 vs.tau = a.qs.tau_leaf + (vs.cbase / CH) * NC;
             }
-            merge_chunk<T, NC, RPL, WQ, TIn>(c, Rs, red, q, p, pf, vs);
+        };
+        // full chunks in a row are prefetched; the first one and a partial last
+        // one are loaded here, row by row inside the leaf
+        for (int64_t t = 0; t < nchunks;) {
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const int64_t row = r0 + t * CH + p + 16 * r;
+                const bool ok = row < r1;
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    const int k = 4 * s + q;
+                    c.put(r, s, (ok && k < a.n) ? (T)a.A[row + (int64_t)k * a.lda] : T(0));
+                }
+            }
+            for (; t + 1 < nfull; ++t) {
+                Prefetch<T, RPL, TIn> pf = make_prefetch<T, RPL, TIn>(a.A, a.lda, a.n, r0 + (t + 1) * CH, q, p);
+                sink(t);
+                leaf_chunk<T, NC, RPL, WQ, true, TIn>(c, Rs, red, q, p, pf, vs);
+            }
+            Prefetch<T, RPL, TIn> none{};
+            sink(t);
+            leaf_chunk<T, NC, RPL, WQ, false, TIn>(c, Rs, red, q, p, none, vs);
+            ++t;
         }
     }
     wave_sync();
@@ -607,32 +529,19 @@ __device__ __forceinline__ void tree_phase(const LeafTreeArgs<T, TIn>& a, int le
         __threadfence();
         if (lane == 0) a.tickets[id] = 0u;      // both arrived: reset for the next call
 
-        T v[NC];
+        // the right (lower) operand in registers, the left one in LDS, so that
+        // the lower index is on top
+        Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS> c;
         if (is_left) {
-            triangle_to_lds<T, NC>(a.tri + (int64_t)partner * NT, red);
-            wave_sync();
-            triangle_column<T, NC>(red, v);
+            triangle_chunk<T, NC>(a.tri + (int64_t)partner * NT, c);
         } else {
-            // this wavefront holds the right (lower) operand: move it to registers
-            // and bring the left one into LDS, keeping the lower index on top
-            triangle_column<T, NC>(Rs, v);
+            triangle_chunk<T, NC>(Rs, c);
             wave_sync();
             triangle_to_lds<T, NC>(a.tri + (int64_t)partner * NT, Rs);
         }
         wave_sync();
-        if constexpr (WQ) {
-            // the operator's reflectors: V (the R2 parts, column `lane` in v)
-            // and tau (written to LDS by the merge)
-            merge_columns<T, NC, Mode::Operator>(v, Rs, red);
-            wave_sync();
-            T* vn = a.qs.Vn + (int64_t)id * NT;
-#pragma unroll
-            for (int i = 0; i < NC; ++i)
-                if (i <= lane && lane < NC) vn[Tri<NC>::off(i) + lane - i] = v[i];
-            if (lane < NC) a.qs.tau_node[(int64_t)id * NC + lane] = red[lane];
-        } else {
-            merge_columns<T, NC, Mode::Merge>(v, Rs, nullptr);
-        }
+        merge_panels<T, NC, WQ>(c, Rs, red, WQ ? a.qs.Vn + (int64_t)id * NT : nullptr,
+                                WQ ? a.qs.tau_node + (int64_t)id * NC : nullptr);
         wave_sync();
         node = left;
         ++level;
@@ -690,12 +599,29 @@ __device__ __forceinline__ int xcd_local_leaf(int g, int P)
     return x * a + (x < b ? x : b) + g / kXcds;
 }
 
+// Wavefronts per SIMD the register budget is held to: two where the chunk leaves
+// room for the working set of a panel
+template <typename T, int NC, int RPL>
+struct LeafWaves {
+    static constexpr int kChunkRegs = RPL * Slots<NC>::NS * (int)(sizeof(T) / 4);
+    static constexpr int kPerSimd = kChunkRegs <= 184 ? 2 : 1;
+};
+
 template <typename T, int NC, int RPL, bool WQ = false>
-__global__ void __launch_bounds__(kWave) tsqr_leaf_tree_kernel(LeafTreeArgs<T> a)
+__global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_leaf_tree_kernel(LeafTreeArgs<T> a)
 {
     __shared__ T Rs[Tri<NC>::kPadded];
-    __shared__ T red[LdsScratch<NC>::kElems];
+    __shared__ __align__(16) T red[PanelLds<T, (RPL > 4 ? RPL : 4)>::kElems];
     leaf_tree_body<T, NC, RPL, WQ>(a, xcd_local_leaf(blockIdx.x, a.leaves), Rs, red);
+}
+
+// Rs := qr([Rs; R2]), both triangles packed in LDS
+template <typename T, int NC>
+__device__ __forceinline__ void merge_lds(const T* R2, T* Rs, T* work)
+{
+    Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS> c;
+    triangle_chunk<T, NC>(R2, c);
+    merge_panels<T, NC, false>(c, Rs, work, nullptr, nullptr);
 }
 
 // Four leaves per workgroup, one wavefront each (one per SIMD of a compute
@@ -705,39 +631,33 @@ __global__ void __launch_bounds__(kWave) tsqr_leaf_tree_kernel(LeafTreeArgs<T> a
 // on a 1024-leaf tree, that global handoff costs 26 us at level 0 and 14 us at
 // level 1, where every wavefront fences at once, against 2-6 us above.  The
 // merges take the same operands in the same order (the lower index on top),
-// so R is bit-identical to tsqr_leaf_tree_kernel's.  P must be a multiple of
-// 4; groups are numbered XCD-locally as single leaves are.
+// so R is bit-identical to tsqr_leaf_tree_kernel's.  The wavefronts of the last
+// workgroup past the last leaf only keep the barriers; with at most four leaves
+// no tree counter is touched.  Groups are numbered XCD-locally as single leaves
+// are.
 template <typename T, int NC, int RPL>
-__global__ void __launch_bounds__(4 * kWave) tsqr_leaf_tree4_kernel(LeafTreeArgs<T> a)
+__global__ void __launch_bounds__(4 * kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_leaf_tree4_kernel(LeafTreeArgs<T> a)
 {
     __shared__ T Rs[4][Tri<NC>::kPadded];
-    __shared__ T red[4][LdsScratch<NC>::kElems];
+    __shared__ __align__(16) T red[4][PanelLds<T, (RPL > 4 ? RPL : 4)>::kElems];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));   // uniform per wavefront
-    const int base = 4 * xcd_local_leaf(blockIdx.x, a.leaves / 4);
+    const int base = 4 * xcd_local_leaf(blockIdx.x, (a.leaves + 3) / 4);
     const int leaf = base + w;
-    leaf_phase<T, NC, RPL>(a, leaf, Rs[w], red[w]);
+    if (leaf < a.leaves) leaf_phase<T, NC, RPL>(a, leaf, Rs[w], red[w]);
     __syncthreads();
     // level 0: leaf base + w (w even) takes base + w + 1 from below
     if ((w & 1) == 0) {
-        T v[NC];
-        triangle_column<T, NC>(Rs[w + 1], v);
-        wave_sync();
-        merge_columns<T, NC, Mode::Merge>(v, Rs[w], nullptr);
-        wave_sync();
-    } else if (a.stamps && lane_id() == 0) {
+        if (leaf + 1 < a.leaves) merge_lds<T, NC>(Rs[w + 1], Rs[w], red[w]);
+    } else if (a.stamps && leaf < a.leaves && lane_id() == 0) {
         a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
         a.stamps[4 * leaf + 3] = 0;
     }
     __syncthreads();
     // level 1: base takes base + 2, then the tree goes on through memory
     if (w == 0) {
-        T v[NC];
-        triangle_column<T, NC>(Rs[2], v);
-        wave_sync();
-        merge_columns<T, NC, Mode::Merge>(v, Rs[0], nullptr);
-        wave_sync();
+        if (base + 2 < a.leaves) merge_lds<T, NC>(Rs[2], Rs[0], red[0]);
         tree_phase<T, NC>(a, leaf, base, 2, Rs[0], red[0]);
-    } else if (w == 2 && a.stamps && lane_id() == 0) {
+    } else if (w == 2 && a.stamps && leaf < a.leaves && lane_id() == 0) {
         a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
         a.stamps[4 * leaf + 3] = 1;
     }
@@ -756,10 +676,10 @@ __global__ void __launch_bounds__(4 * kWave) tsqr_leaf_tree4_kernel(LeafTreeArgs
 // whatever merges it performed) to stamps[2g], stamps[2g + 1], which measures
 // the schedule.  TIn is the storage type of A.
 template <typename T, int NC, int RPL, typename TIn = T>
-__global__ void __launch_bounds__(kWave) tsqr_batch_kernel(BatchArgs<T, TIn> b)
+__global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_batch_kernel(BatchArgs<T, TIn> b)
 {
     __shared__ T Rs[Tri<NC>::kPadded];
-    __shared__ T red[LdsScratch<NC>::kElems];
+    __shared__ __align__(16) T red[PanelLds<T, (RPL > 4 ? RPL : 4)>::kElems];
     const uint64_t t_start = b.stamps ? (uint64_t)wall_clock64() : 0;
     const BatchTile t = b.tiles[blockIdx.x];
     if (b.run_if && b.run_if[t.inst] == 0) return;

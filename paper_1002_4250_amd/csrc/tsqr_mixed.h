@@ -102,11 +102,6 @@ __device__ inline double substitution_operand(const float* Rt, int n, int p, int
     return x[k];
 }
 
-__device__ __forceinline__ double mfma4(double a, double b, double c)
-{
-    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
-}
-
 constexpr int kGramWaves = 2;
 
 // The work of one wavefront of the Gram kernel: the substitution of its own

@@ -1,0 +1,665 @@
+// tsqr_panel.h -- one panel of a Householder factorization on the FP64 matrix
+// cores: the building block of the leaves and of the reduction tree.
+//
+// R := R-factor of [R; C], R an NC x NC triangle in LDS (packed by rows), C a
+// block of 16 RB rows in the registers of one wavefront, four columns (a panel)
+// at a time.  With X = C(:, 4P..4P+3), the four reflectors of the panel
+//     v_j = [e_j; s_j x_j],   x_j = X(:, j) after the panel's reflectors before j
+// need only inner products of X with the trailing columns, never the columns
+// themselves:
+//   1. G = X^T [X, C_trailing], one matrix product over the rows of C;
+//   2. per reflector j, with sigma^2 = G(j, j) and d = G(j, :),
+//        beta = -sgn sqrt(alpha^2 + sigma^2),  w = R(j, :) + s d,
+//        R(j, :) -= tau w,   f = tau s w,
+//      and the products that are left follow x_i := x_i - f_i x_j and
+//      c := c - f x_j:   G(i, :) -= f_i G(j, :) + f (G(j, i) - f_i sigma^2);
+//   3. C_trailing -= X F, one matrix product, with F from f by back
+//      substitution (x_j in terms of the columns of X).
+// Steps 1 and 3 are the arithmetic (2 m n^2 flops over a whole matrix); step 2
+// works on 4 x NC numbers, one column per lane, with no cross-lane reduction
+// and no exchange through LDS, so a panel has one dependent chain of four
+// reflectors instead of four chains with a reduction over the rows in each.
+//
+// Step 2 computes sigma_i^2 from inner products of columns that still contain
+// their components along x_j, j < i, so it loses accuracy by the factor
+//     growth = sum_j (f_i ||x_j||)^2 / (alpha_i^2 + sigma_i^2).
+// Where growth exceeds kMaxGrowth the panel is cut in front of column i: the
+// reflectors found so far are applied to all columns from i on, and the rest of
+// the panel starts again from fresh inner products.  A panel of one column
+// is the plain Householder step, so nothing is assumed about C; the bound only
+// decides how many passes a panel takes (uniform or moderately conditioned
+// columns take one).
+//
+// Register layout.  The matrix instruction is the 4x4x4 FP64 product with four
+// independent blocks, D_b = A_b B_b + C_b.  Writing lane l as 16 d2 + 4 d1 + d0,
+// block b lies in the lanes with d1 = b, and
+//     A_b(i, k) from lane (d2 = k, d0 = i),  B_b(k, j) from lane (d2 = k, d0 = j),
+//     D_b(i, j) to lane (d2 = i, d0 = j).
+// c[rb][s] holds rows 16 rb + 4 d1 + d2 of columns 4 s + d0.  So a register
+// of C is a B operand (and a register of X an A operand) of step 1 as it stands
+// and the C/D operand of step 3: the trailing columns never move.  Only X moves,
+// d2 <-> d0, through LDS, to be the A operand of step 3.  The four blocks of G
+// are partial sums; they are added within the 16-lane rows by DPP and the result
+// is transposed to one column per lane with the row swaps of gfx950.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "tsqr_internal.h"
+
+namespace tsqr {
+namespace dev {
+
+using float4v = float __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double mfma4(double a, double b, double c)
+{
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ float4v mfma4(float a, float b, float4v c)
+{
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+
+// Placed between matrix instructions and a branch.  Reading a matrix result
+// needs up to 9 wait states that the compiler has to insert.  It does so
+// within a basic block, but a register copy that its allocator placed at the
+// start of the block behind a branch was found reading the result of the last
+// instruction before that branch with one wait state between, and took the old
+// value.
+__device__ __forceinline__ void mfma_settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7\n\ts_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The registers of a chunk of 16 RPL rows and 4 NS columns, and where they lie:
+// register (r, s) holds row 16 r + p, column 4 s + q of the lane (q, p).
+template <typename T, int RPL, int NS>
+struct Chunk;
+
+template <int RPL, int NS>
+struct Chunk<double, RPL, NS> {
+    double v[RPL][NS];
+    __device__ __forceinline__ double get(int r, int s) const { return v[r][s]; }
+    __device__ __forceinline__ void put(int r, int s, double x) { v[r][s] = x; }
+    static __device__ __forceinline__ int q(int lane) { return lane & 3; }
+    static __device__ __forceinline__ int p(int lane) { return (lane & 12) + (lane >> 4); }
+};
+
+template <int RPL, int NS>
+struct Chunk<float, RPL, NS> {
+    static constexpr int RV = (RPL + 3) / 4;     // four rows make up one accumulator
+    float4v v[RV][NS];
+    __device__ __forceinline__ float get(int r, int s) const { return v[r / 4][s][r % 4]; }
+    __device__ __forceinline__ void put(int r, int s, float x) { v[r / 4][s][r % 4] = x; }
+    static __device__ __forceinline__ int q(int lane) { return lane & 3; }
+    static __device__ __forceinline__ int p(int lane) { return lane >> 2; }
+};
+
+// LDS work area of one wavefront.  FP64: F (4 rows, stride kFStride so that the
+// four rows read together lie in different banks), then X with d2 and d0
+// exchanged.  FP32: F, the four coefficients of a column together.
+constexpr int kFStride = 68;
+// FP64: position of (d2 = k, d1, d0 = i) of a row block of X at kXOff(k) + 4 d1 + i,
+// with the four k apart so that neither the writes (i varies slowest over the
+// lanes) nor the reads (k slowest) of half a wavefront meet in a bank
+constexpr int kXBlock = 84;
+__device__ __forceinline__ int x_offset(int k) { return 18 * (k & 1) + 48 * (k >> 1); }
+template <typename T, int RPL>
+struct PanelLds {
+    static constexpr int kElems = sizeof(T) == 8 ? 4 * kFStride + RPL * kXBlock : 4 * kWave;
+};
+
+// Row blocks of 16 of a triangle as the bottom operand of a merge
+template <typename T, int NC>
+struct MergeRows {
+    static constexpr int RB = sizeof(T) == 8 ? (4 * Slots<NC>::NS + 15) / 16 : 4;
+};
+
+constexpr int kMaxGrowth = 16;
+
+// old with the banks (quads of a 16-lane row) in BANKS replaced by x moved by CTRL
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double dpp_into(double old, double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(x), CTRL, 0xF, BANKS, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(x), CTRL, 0xF, BANKS, false);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL, int BANKS>
+__device__ __forceinline__ float dpp_into(float old, float x)
+{
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), CTRL, 0xF, BANKS, false));
+}
+
+// Sums over the four quads of each 16-lane row of a, b, c, d: the sum of a in
+// quad 0, of b in quad 1, of c in quad 2, of d in quad 3.
+__device__ __forceinline__ double quad_sums(double a, double b, double c, double d)
+{
+    // ac: quads 0, 1 hold a0 + a2, a1 + a3; quads 2, 3 hold c0 + c2, c1 + c3
+    const double ac = dpp_into<0xE4, 0xC>(a, c) + dpp_into<0x128, 0xC>(dpp_mov<0x128>(a), c);
+    const double bd = dpp_into<0xE4, 0xC>(b, d) + dpp_into<0x128, 0xC>(dpp_mov<0x128>(b), d);
+    // even quads add their right neighbour in ac, odd quads their left one in bd
+    return dpp_into<0xE4, 0xA>(ac, bd) + dpp_into<0x124, 0xA>(dpp_mov<0x12C>(ac), bd);
+}
+// (in FP32 an addition takes its operand through DPP, so adding first and
+// merging afterwards is shorter)
+__device__ __forceinline__ float quad_sums(float a, float b, float c, float d)
+{
+    const float ac = dpp_into<0xE4, 0xC>(a + dpp_mov<0x128>(a), c + dpp_mov<0x128>(c));
+    const float bd = dpp_into<0xE4, 0xC>(b + dpp_mov<0x128>(b), d + dpp_mov<0x128>(d));
+    return dpp_into<0xE4, 0xA>(ac + dpp_mov<0x12C>(ac), bd + dpp_mov<0x124>(bd));
+}
+
+// The sum over the four quads of each 16-lane row, in all four.
+template <typename T>
+__device__ __forceinline__ T quad_sum(T a)
+{
+    a = a + dpp_mov<0x128>(a);
+    return a + dpp_mov<0x124>(a);
+}
+
+// a.rows 1, 3 <-> b.rows 0, 2 (16-lane rows)
+__device__ __forceinline__ void swap_rows16(double& a, double& b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double((int)hi[0], (int)lo[0]);
+    b = __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ void swap_rows16(float& a, float& b)
+{
+    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+    a = __int_as_float((int)x[0]);
+    b = __int_as_float((int)x[1]);
+}
+// a.rows 2, 3 <-> b.rows 0, 1
+__device__ __forceinline__ void swap_rows32(double& a, double& b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double((int)hi[0], (int)lo[0]);
+    b = __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ void swap_rows32(float& a, float& b)
+{
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+    a = __int_as_float((int)x[0]);
+    b = __int_as_float((int)x[1]);
+}
+
+// 4 x 4 transpose of the quads' registers and lanes: out[k] of lane i is in[i]
+// of lane k (lanes numbered within a quad).
+__device__ __forceinline__ float4v quad_transpose(float4v x, int lane)
+{
+    const bool odd = lane & 1, high = lane & 2;
+    // quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E; the moves run in every lane, ahead of the selects
+    const float x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+    const float m0 = dpp_mov<0xB1>(x0), m1 = dpp_mov<0xB1>(x1), m2 = dpp_mov<0xB1>(x2), m3 = dpp_mov<0xB1>(x3);
+    const float a0 = odd ? m1 : x0, a1 = odd ? x1 : m0, a2 = odd ? m3 : x2, a3 = odd ? x3 : m2;
+    const float b0 = dpp_mov<0x4E>(a0), b1 = dpp_mov<0x4E>(a1), b2 = dpp_mov<0x4E>(a2), b3 = dpp_mov<0x4E>(a3);
+    return float4v{high ? b2 : a0, high ? b3 : a1, high ? a2 : b0, high ? a3 : b1};
+}
+
+// Step 1 of a panel: g[i] = X(:, i) . C(:, lane), one column per lane, for the
+// columns of slots [S0, S1) of C (other lanes get values that nothing uses), X
+// slot A of x.  Only the first RA row blocks take part.
+template <int S0, int S1>
+struct Groups {
+    static constexpr int T0 = S0 / 4, T1 = (S1 + 3) / 4;         // live groups of 16 columns
+    // slots outside [S0, S1) are not needed: any live one stands in
+    static constexpr int live(int s) { return s < S0 ? S0 : (s >= S1 ? S1 - 1 : s); }
+};
+
+template <int A, int S0, int S1, int RA, int RB, int NX, int NS>
+__device__ __forceinline__ void panel_products(const Chunk<double, RB, NX>& x, const Chunk<double, RB, NS>& c,
+                                               double (&g)[4])
+{
+    using Gr = Groups<S0, S1>;
+    constexpr int T0 = Gr::T0, T1 = Gr::T1;
+    double G[NS];
+#pragma unroll
+    for (int rb = 0; rb < RA; ++rb)
+        static_for<S0, S1>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            G[s] = mfma4(x.v[rb][A], c.v[rb][s], rb == 0 ? 0.0 : G[s]);
+        });
+    // add the four blocks; column 16 t + 4 b + j of row i of G to lane (d2 = i, d1 = b, d0 = j) of g[t]
+    static_for<T0, T1>([&](auto tc) {
+        constexpr int t = decltype(tc)::value, a = 4 * t;
+        if constexpr (Gr::live(a) == Gr::live(a + 3))
+            g[t] = quad_sum(G[Gr::live(a)]);
+        else
+            g[t] = quad_sums(G[Gr::live(a)], G[Gr::live(a + 1)], G[Gr::live(a + 2)], G[Gr::live(a + 3)]);
+    });
+    static_for<0, T0>([&](auto tc) { g[decltype(tc)::value] = g[T0]; });
+    static_for<T1, 4>([&](auto tc) { g[decltype(tc)::value] = g[T1 - 1]; });
+    // transpose t and d2
+    swap_rows16(g[0], g[1]);
+    swap_rows16(g[2], g[3]);
+    swap_rows32(g[0], g[2]);
+    swap_rows32(g[1], g[3]);
+}
+
+template <int A, int S0, int S1, int RA, int RB, int NX, int NS>
+__device__ __forceinline__ void panel_products(const Chunk<float, RB, NX>& x, const Chunk<float, RB, NS>& c,
+                                               float (&g)[4])
+{
+    using Gr = Groups<S0, S1>;
+    constexpr int T0 = Gr::T0, T1 = Gr::T1;
+    float4v G[NS];
+    static_for<S0, S1>([&](auto sc) { G[decltype(sc)::value] = float4v{0.0f, 0.0f, 0.0f, 0.0f}; });
+#pragma unroll
+    for (int r = 0; r < RA; ++r)
+        static_for<S0, S1>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            G[s] = mfma4((float)x.v[r / 4][A][r % 4], (float)c.v[r / 4][s][r % 4], G[s]);
+        });
+    // add the sixteen blocks: within the 16-lane rows, then over the rows, slot s
+    // ending in quad s
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float t4[4];
+        static_for<T0, T1>([&](auto tc) {
+            constexpr int t = decltype(tc)::value, a = 4 * t;
+            if constexpr (Gr::live(a) == Gr::live(a + 3))
+                t4[t] = quad_sum((float)G[Gr::live(a)][i]);
+            else
+                t4[t] = quad_sums((float)G[Gr::live(a)][i], (float)G[Gr::live(a + 1)][i],
+                                  (float)G[Gr::live(a + 2)][i], (float)G[Gr::live(a + 3)][i]);
+        });
+        static_for<0, T0>([&](auto tc) { t4[decltype(tc)::value] = t4[T0]; });
+        static_for<T1, 4>([&](auto tc) { t4[decltype(tc)::value] = t4[T1 - 1]; });
+        swap_rows16(t4[0], t4[1]);
+        swap_rows16(t4[2], t4[3]);
+        float u = t4[0] + t4[1], v = t4[2] + t4[3];
+        swap_rows32(u, v);
+        g[i] = u + v;
+    }
+}
+
+// The reflectors of a panel (step 2), one column of [R; C] per lane: g[j] are
+// the inner products of X(:, j) with the lane's column, r[j] row 4P + j of R.
+// Columns below lo are done already.  On return r holds the new rows, nf the
+// coefficients -F in terms of the columns of X (zero for columns outside
+// [lo, hi)), tau and s the reflectors' scalars, and the result is hi: NJ, or
+// the column in front of which the panel was cut.
+//
+// With y = 1/sqrt(alpha^2 + sigma^2), z = |alpha| y and q = 1/(1 + z):
+//     tau = 1 + z,  s = sgn y q,  tau s = sgn y,  R(j, :) - tau w = -(z R(j, :) + sgn y d),
+// y and q from the hardware estimates (about 2^-24 on gfx950 in FP64, 1 ulp in
+// FP32) by one third-order step each, which leaves 2^-72 (FP32: second-order).
+template <typename T>
+__device__ __forceinline__ T refined_rsq(T S)
+{
+    const T y = hw_rsq(S);
+    const T e = fmadd(-S * y, y, T(1));
+    return fmadd(y * e, sizeof(T) == 8 ? fmadd(e, T(0.375), T(0.5)) : T(0.5), y);
+}
+template <typename T>
+__device__ __forceinline__ T refined_rcp(T u)
+{
+    const T q = hw_rcp(u);
+    const T e = fmadd(-u, q, T(1));
+    return fmadd(q, sizeof(T) == 8 ? fmadd(e, e, e) : e, q);
+}
+
+// The scalars of one reflector: z, q and sgn y (see above).  S = 0 (a zero
+// column below a zero alpha) gives z = 0 and finite y, q.
+template <typename T>
+struct PanelScalars {
+    T z, q, sy;
+};
+template <typename T>
+__device__ __forceinline__ PanelScalars<T> panel_scalars(T alpha, T S)
+{
+#pragma clang fp contract(off)
+    PanelScalars<T> h;
+    const T y = refined_rsq(maxv(S, Limits<T>::tiny));
+    h.z = absv(alpha) * y;
+    h.q = refined_rcp(T(1) + h.z);
+    h.sy = copysignv(y, alpha);
+    return h;
+}
+
+// Reflector j of a panel on the lane's column: its row of R, the coefficient
+// nf = -tau s w, and the products that are left.  n[j][i] is -f of column
+// J0 + i, grow the sum over the reflectors of (f sigma)^2.
+template <typename T, int J0, int NJ, int j, bool Mask>
+__device__ __forceinline__ void panel_apply(const PanelScalars<T>& h, T sigma2, T (&g)[4], T (&r)[4], T (&nf)[4],
+                                            T (&n)[4][4], T& grow, int lane)
+{
+#pragma clang fp contract(off)
+    const T w = fmadd(h.sy * h.q, g[j], r[j]);
+    r[j] = fmadd(-h.z, r[j], -h.sy * g[j]);
+    nf[j] = -h.sy * w;
+    if constexpr (Mask) nf[j] = lane > J0 + j ? nf[j] : T(0);
+    if constexpr (j + 1 < NJ) {
+        const T p = nf[j] * sigma2;
+        const T hv = g[j] + p;            // x_j . (the lane's column after reflector j)
+        grow = fmadd(nf[j], p, grow);
+#pragma unroll
+        for (int i = j + 1; i < NJ; ++i) {
+            n[j][i] = lane_value(nf[j], J0 + i);
+            const T hi = lane_value(hv, J0 + i);
+            g[i] = fmadd(nf[j], hi, fmadd(n[j][i], g[j], g[i]));
+        }
+    }
+}
+
+// F: c - sum_j f_j x_j with x_j = X(:, j) - sum_{i<j} f_ij x_i
+template <typename T, int NJ>
+__device__ __forceinline__ void panel_coefficients(T (&nf)[4], const T (&n)[4][4])
+{
+#pragma unroll
+    for (int j = NJ - 2; j >= 0; --j)
+#pragma unroll
+        for (int i = j + 1; i < NJ; ++i) nf[j] = fmadd(n[j][i], nf[i], nf[j]);
+}
+
+// All reflectors of a panel at once.  Returns false, with g and r spoilt, where
+// the panel has to be cut (growth) or a column calls for an identity reflector
+// (one whose sum of squares is below the smallest normal number; a zero
+// column below a zero alpha does no harm here).
+template <typename T, int NC, int P>
+__device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4])
+{
+    constexpr int J0 = 4 * P;
+    constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
+    T n[4][4], alpha[4], sigma2[4];
+    T grow = T(0), least = T(0);
+    uint64_t over = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nf[j] = T(0);
+    static_for<0, NJ>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        alpha[j] = lane_value(r[j], J0 + j);
+        sigma2[j] = lane_value(g[j], J0 + j);
+        const T S = fmadd(alpha[j], alpha[j], sigma2[j]);
+        least = j == 0 ? sigma2[j] : minv(sigma2[j], least);
+        if constexpr (j > 0)
+            over |= __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) & ((uint64_t)1 << (J0 + j));
+        const PanelScalars<T> h = panel_scalars(alpha[j], S);
+        panel_apply<T, J0, NJ, j, false>(h, sigma2[j], g, r, nf, n, grow, 0);
+    });
+    panel_coefficients<T, NJ>(nf, n);
+    bool good = over == 0;
+    if (__builtin_amdgcn_ballot_w64(least < Limits<T>::tiny) != 0) [[unlikely]] {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (__builtin_amdgcn_ballot_w64(sigma2[j] < Limits<T>::tiny && (sigma2[j] > T(0) || alpha[j] != T(0))) != 0)
+                good = false;
+    }
+    return good;
+}
+
+// The general form: columns below lo are done already; the panel is cut in
+// front of the first column (after lo) whose growth is over the limit, and the
+// result is that column, or NJ.  nf is zero for columns outside [lo, hi); in the
+// lanes of columns left of hi it is valid with WQ only.
+template <typename T, int NC, int P, bool WQ>
+__device__ __forceinline__ int panel_reflectors_cut(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4],
+                                                    int lane, int lo)
+{
+    constexpr int J0 = 4 * P;
+    constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
+    T n[4][4];
+    T grow = T(0);
+    int hi = NJ;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nf[j] = tau[j] = s[j] = T(0);
+    static_for<0, NJ>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const T alpha = lane_value(r[j], J0 + j);
+        const T sigma2 = lane_value(g[j], J0 + j);
+        const T S = fmadd(alpha, alpha, sigma2);
+        if constexpr (j > 0) {
+            const uint64_t over = __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S));
+            if (((over >> (J0 + j)) & 1) && j > lo && j < hi) hi = j;
+        }
+        PanelScalars<T> h = panel_scalars(alpha, S);
+        if (__builtin_amdgcn_ballot_w64(sigma2 >= Limits<T>::tiny) == 0 || j < lo || j >= hi) [[unlikely]] {
+            h.z = T(-1);                  // an identity reflector
+            h.sy = T(0);
+        }
+        s[j] = h.sy * h.q;
+        tau[j] = T(1) + h.z;
+        panel_apply<T, J0, NJ, j, WQ>(h, sigma2, g, r, nf, n, grow, lane);
+    });
+    panel_coefficients<T, NJ>(nf, n);
+    return hi;
+}
+
+// Step 3 of a panel: the columns of slot s (and, for WQ, the panel's own
+// reflectors) from F in LDS and X in the layout of an A operand.
+template <typename T, int RA>
+struct PanelUpdate;
+
+template <int RA>
+struct PanelUpdate<double, RA> {
+    double xt[RA];
+    const double* fr;
+    template <typename C>
+    static __device__ __forceinline__ void stage(const C& c, int P, double* work, int lane)
+    {
+        double* x = work + 4 * kFStride + x_offset(lane & 3) + (lane & 12) + (lane >> 4);
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) x[rb * kXBlock] = c.v[rb][P];
+    }
+    static __device__ __forceinline__ void put_f(double* work, int lane, const double (&nf)[4])
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) work[j * kFStride + lane] = nf[j];
+    }
+    template <typename C>
+    __device__ __forceinline__ PanelUpdate(const C&, int, const double* work, int lane)
+        : fr(work + (lane >> 4) * kFStride + (lane & 3))
+    {
+        const double* x = work + 4 * kFStride + x_offset(lane >> 4) + (lane & 15);
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) xt[rb] = x[rb * kXBlock];
+    }
+    template <typename C>
+    __device__ __forceinline__ void apply(C& c, int s) const
+    {
+        const double f = fr[4 * s];
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) c.v[rb][s] = mfma4(xt[rb], f, c.v[rb][s]);
+    }
+    // the panel's own columns from column hi on
+    template <typename C>
+    __device__ __forceinline__ void apply_from(C& c, int s, int lane, int hi) const
+    {
+        double fs = fr[4 * s];
+        asm volatile("" : "+v"(fs));      // read in every lane, no branch around the read
+        const double f = (lane & 3) >= hi ? fs : 0.0;
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) c.v[rb][s] = mfma4(xt[rb], f, c.v[rb][s]);
+    }
+    // row block rb of the vectors v_j = s_j x_j, x_j = X(:, j) + sum_{i<j} nf_i(J0 + j) X(:, i)
+    template <typename Keep>
+    __device__ __forceinline__ void reflectors(int P, int lane, const double (&s)[4], Keep&& keep) const
+    {
+        const int d0 = lane & 3, d2 = lane >> 4;
+        const double sd = d0 == 0 ? s[0] : d0 == 1 ? s[1] : d0 == 2 ? s[2] : s[3];
+        const double f = d2 < d0 ? fr[4 * P] * sd : (d2 == d0 ? sd : 0.0);
+        double v[RA];
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) v[rb] = mfma4(xt[rb], f, 0.0);
+        mfma_settle();
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) keep(rb, v[rb]);
+    }
+};
+
+template <int RA>
+struct PanelUpdate<float, RA> {
+    static constexpr int RV = (RA + 3) / 4;
+    float4v xt[RV];
+    const float4v* fr;
+    template <typename C>
+    static __device__ __forceinline__ void stage(const C&, int, float*, int)
+    {
+    }
+    static __device__ __forceinline__ void put_f(float* work, int lane, const float (&nf)[4])
+    {
+        reinterpret_cast<float4v*>(work)[lane] = float4v{nf[0], nf[1], nf[2], nf[3]};
+    }
+    template <typename C>
+    __device__ __forceinline__ PanelUpdate(const C& c, int P, const float* work, int lane)
+        : fr(reinterpret_cast<const float4v*>(work) + (lane & 3))
+    {
+#pragma unroll
+        for (int r = 0; r < RV; ++r) xt[r] = quad_transpose(c.v[r][P], lane);
+    }
+    template <typename C>
+    __device__ __forceinline__ void apply(C& c, int s) const
+    {
+        const float4v f = fr[4 * s];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int r = 0; r < RV; ++r) c.v[r][s] = mfma4((float)xt[r][k], (float)f[k], c.v[r][s]);
+    }
+    template <typename C>
+    __device__ __forceinline__ void apply_from(C& c, int s, int lane, int hi) const
+    {
+        const bool on = (lane & 3) >= hi;
+        const float4v f = fr[4 * s];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int r = 0; r < RV; ++r) c.v[r][s] = mfma4((float)xt[r][k], on ? (float)f[k] : 0.0f, c.v[r][s]);
+    }
+    template <typename Keep>
+    __device__ __forceinline__ void reflectors(int P, int lane, const float (&s)[4], Keep&& keep) const
+    {
+        const int j = lane & 3;
+        const float sd = j == 0 ? s[0] : j == 1 ? s[1] : j == 2 ? s[2] : s[3];
+        const float4v nf = fr[4 * P];
+        float4v x[RV];
+#pragma unroll
+        for (int r = 0; r < RV; ++r) x[r] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float f = k < j ? (float)nf[k] * sd : (k == j ? sd : 0.0f);
+#pragma unroll
+            for (int r = 0; r < RV; ++r) x[r] = mfma4((float)xt[r][k], f, x[r]);
+        }
+        mfma_settle();
+#pragma unroll
+        for (int r = 0; r < RA; ++r) keep(r, (float)x[r / 4][r % 4]);
+    }
+};
+
+// One panel, see the top of the file.  Only the first RA row blocks are
+// nonzero in the panel's columns.  keep(rb, v, tau, lo, hi) receives the
+// chunk part of the panel's reflectors where WQ is set: v = s_j x_j in the
+// layout of c, valid for the columns q in [lo, hi).
+template <typename T, int NC, int RB, int RA, int P, bool WQ, typename Keep>
+__device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs, T* work, Keep&& keep)
+{
+    constexpr int NS = Slots<NC>::NS;
+    constexpr int J0 = 4 * P;
+    constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
+    using Update = PanelUpdate<T, RA>;
+    const int lane = lane_id();
+    T* Rl = Rs + lane;
+    // lo < 0: all reflectors at once; otherwise from column lo on, with cuts
+    int lo = WQ ? 0 : -1, hi;
+    do {
+        // rows J0.. of R, one column per lane (lanes left of the diagonal and
+        // past NC read other entries of the padded triangle; nothing uses them)
+        T r[4], g[4], nf[4], tau[4], s[4];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) r[j] = Rl[Tri<NC>::off(J0 + j) - (J0 + j)];
+        Update::stage(c, P, work, lane);
+        lds_order();
+        panel_products<P, P, NS, RA>(c, c, g);
+        hi = NJ;
+        if (!WQ && lo < 0) {
+            if (!panel_reflectors<T, NC, P>(g, r, nf)) [[unlikely]] {
+                lo = 0;
+                hi = 0;
+                continue;
+            }
+        } else {
+            hi = panel_reflectors_cut<T, NC, P, WQ>(g, r, nf, tau, s, lane, lo);
+        }
+        // last row first: a lane left of a row's diagonal writes into the end of
+        // the row before, which the next store writes again.  (The lane passes
+        // through an opaque copy so that the compiler does not keep one mask per
+        // panel alive over the whole chunk.)
+        int col = lane;
+        asm volatile("" : "+v"(col));
+        if ((unsigned)(col - J0) < (unsigned)(NC - J0)) {
+#pragma unroll
+            for (int j = NJ - 1; j >= 0; --j) {
+                Rl[Tri<NC>::off(J0 + j) - (J0 + j)] = r[j];
+                asm volatile("" ::: "memory");
+            }
+        }
+        Update::put_f(work, lane, nf);
+        lds_order();
+        const Update up(c, P, work, lane);
+        static_for<P + 1, NS>([&](auto sc) { up.apply(c, decltype(sc)::value); });
+        mfma_settle();
+        if constexpr (WQ) up.reflectors(P, lane, s, [&](int rb, T v) { keep(rb, v, tau, lo, hi); });
+        if (hi < NJ) [[unlikely]] {
+            up.apply_from(c, P, lane, hi);
+            mfma_settle();
+        }
+        lds_order();
+        lo = hi;
+    } while (hi < NJ);
+}
+
+// R := qr([R; R2]), R packed in LDS, the triangle R2 in c (zero below its
+// diagonal): the operator of section 2 in the structured form of Table 3 (a
+// panel touches only the row blocks of R2 that reach its columns).  With WQ the
+// reflectors' R2 parts go to Vn (packed by rows) and their tau to tau_out.
+template <typename T, int NC, bool WQ>
+__device__ __forceinline__ void merge_panels(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work, T* Vn,
+                                             T* tau_out)
+{
+    constexpr int RB = MergeRows<T, NC>::RB;
+    constexpr int NS = Slots<NC>::NS;
+    const int lane = lane_id();
+    const int q = c.q(lane), p = c.p(lane);
+    static_for<0, NS>([&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        panel_step<T, NC, RB, P / 4 + 1, P, WQ>(c, Rs, work, [&](int rb, T v, const T(&tau)[4], int lo, int hi) {
+            const int i = 16 * rb + p, k = 4 * P + q;
+            if (i <= k && k < NC && q >= lo && q < hi) Vn[Tri<NC>::off(i) + k - i] = v;
+            if (rb == 0 && lane == 0)
+                for (int j = lo; j < hi; ++j) tau_out[4 * P + j] = tau[j];
+        });
+    });
+}
+
+// The triangle tri (packed by rows, LDS or global) as the bottom operand of
+// merge_panels.
+template <typename T, int NC>
+__device__ __forceinline__ void triangle_chunk(const T* tri, Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c)
+{
+    const int lane = lane_id();
+    const int q = c.q(lane), p = c.p(lane);
+#pragma unroll
+    for (int rb = 0; rb < MergeRows<T, NC>::RB; ++rb) {
+        const int i = 16 * rb + p;
+        const int base = Tri<NC>::off(i) - i + q;       // entry (i, 4 s + q) is at base + 4 s
+#pragma unroll
+        for (int s = 0; s < Slots<NC>::NS; ++s) {
+            const int k = 4 * s + q;
+            const bool in = i <= k && k < NC;
+            const T t = 4 * s + 3 < 16 * rb ? T(0) : tri[in ? base + 4 * s : 0];
+            c.put(rb, s, in ? t : T(0));
+        }
+    }
+}
+
+}  // namespace dev
+}  // namespace tsqr
