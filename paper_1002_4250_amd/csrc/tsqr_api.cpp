@@ -68,7 +68,16 @@ constexpr int64_t kAlign = 256;
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+// The tuning table's width for n columns
 int padded_columns(int64_t n)
+{
+    for (int nc : {TSQR_TUNING_NC_VALUES})
+        if (n <= nc) return nc;
+    return -1;
+}
+
+// The smallest compiled width for n columns
+int kernel_columns(int64_t n)
 {
     for (int nc : {TSQR_NC_VALUES})
         if (n <= nc) return nc;
@@ -84,10 +93,18 @@ bool leaf_instance_exists(int dtype, int nc, int rpl)
     return false;
 }
 
+// The smallest width for n columns compiled with this many rows per lane
+int kernel_columns(int64_t n, int dtype, int rpl)
+{
+    for (int nc : {TSQR_NC_VALUES})
+        if (n <= nc && leaf_instance_exists(dtype, nc, rpl)) return nc;
+    return -1;
+}
+
 int elem_bytes(int dtype) { return dtype == TSQR_F64 ? 8 : 4; }
 
 struct Geometry {
-    int nc = 0;
+    int nc = 0;                // compiled width of the kernels
     int rpl = 0;
     int64_t leaf_rows = 0;
     int64_t leaves = 0;
@@ -150,6 +167,7 @@ int plan(const tsqr_handle_s* h, int64_t m, int64_t n, int dtype, Geometry* g, b
             if (g->rpl == 0) return TSQR_ERR_UNSUPPORTED;
         }
     }
+    g->nc = kernel_columns(n, dtype, g->rpl);
     const int64_t chunk = (int64_t)kRowsPerLaneUnit * g->rpl;
     int64_t L;
     if (h->leaf_rows > 0) {
@@ -281,7 +299,7 @@ int qr_uppers(tsqr_handle_t h, int64_t n, T* R1, T* R2, T* tau, void* stream)
     if (n > 0 && !R2) return -4;
     if (n > 0 && !tau) return -5;
     if (n == 0) return 0;
-    const int nc = padded_columns(n);
+    const int nc = kernel_columns(n);
     if (nc < 0) return TSQR_ERR_UNSUPPORTED;
     if (h->planning_only) return TSQR_ERR_NO_DEVICE;
     return hip_status(h, dispatch_op<T>((int)n, nc, R1, R2, tau, static_cast<hipStream_t>(stream)));
@@ -529,7 +547,7 @@ struct tsqr_batch_plan_s {
 namespace {
 int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m, const int64_t* a_offset,
                     const int64_t* lda, int dtype, int force_rpl, tsqr_batch_plan_t* out,
-                    int64_t leaf_rows = 0);
+                    int64_t leaf_rows = 0, bool fill = true);
 }
 
 int tsqr_batch_plan_create(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m, const int64_t* a_offset,
@@ -541,9 +559,11 @@ int tsqr_batch_plan_create(tsqr_handle_t h, int64_t batch, int64_t n, const int6
 namespace {
 // The batched plan; force_rpl (if positive) fixes the rows per lane, as the
 // mixed-precision fallback (compiled at 8 rows per lane only) needs, and
-// leaf_rows (if positive) the leaf size, rounded up to whole chunks.
+// leaf_rows (if positive) the leaf size, rounded up to whole chunks.  `fill`
+// lets the leaf size follow the batch (see below).
 int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m, const int64_t* a_offset,
-                    const int64_t* lda, int dtype, int force_rpl, tsqr_batch_plan_t* out, int64_t leaf_rows)
+                    const int64_t* lda, int dtype, int force_rpl, tsqr_batch_plan_t* out, int64_t leaf_rows,
+                    bool fill)
 {
     if (!h) return -1;
     if (batch < 0) return -2;
@@ -567,7 +587,21 @@ int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m,
     // entry, else 64 chunks (see plan)
     int64_t L = n > 0 ? g.leaf_rows
                       : (h->leaf_rows > 0 ? align_up(h->leaf_rows, kRowsPerLaneUnit) : 64 * kRowsPerLaneUnit);
-    if (n > 0 && leaf_rows > 0) L = align_up(leaf_rows, (int64_t)kRowsPerLaneUnit * g.rpl);
+    if (n > 0 && leaf_rows > 0) {
+        L = align_up(leaf_rows, (int64_t)kRowsPerLaneUnit * g.rpl);
+    } else if (n > 0 && fill && !h->planning_only && h->leaf_rows == 0 && !find_tuning(h, dtype, padded_columns(n), 1, true)) {
+        // a batch that does not fill the device with leaves of 64 chunks lasts
+        // as long as its longest leaf while the other compute units are idle:
+        // cut it into as many leaves as are resident at once (512 instances of
+        // 8 to 20000 rows, n = 32, FP64: 674 us with 64 chunks).  The planning
+        // handle, which has no device to fill, keeps 64 chunks.
+        int64_t rows = 0;
+        for (int64_t b = 0; b < batch && rows < (int64_t)1 << 60; ++b) rows += std::min(m[b], (int64_t)1 << 60);
+        const int64_t target = (int64_t)h->cu_count * leaf_occupancy(h, dtype, g.nc, g.rpl);
+        const int64_t chunk = (int64_t)kRowsPerLaneUnit * g.rpl;
+        const int64_t even = align_up(std::max((rows + target - 1) / target, chunk), chunk);
+        L = std::min(L, even);
+    }
     std::vector<tsqr::BatchInstance> inst((size_t)batch);
     std::vector<tsqr::BatchTile> tiles;
     std::vector<int64_t> tile_rows;
@@ -798,10 +832,9 @@ int64_t mixed_rows_per_block(int64_t batch, int64_t m)
 hipError_t dispatch_fallback(const tsqr::BatchArgs<double, float>& a, int tiles, int nc, hipStream_t s)
 {
     switch (nc) {
-    case 16: return tsqr::launch_batch_f64in32_16(a, tiles, s);
-    case 32: return tsqr::launch_batch_f64in32_32(a, tiles, s);
-    case 50: return tsqr::launch_batch_f64in32_50(a, tiles, s);
-    case 64: return tsqr::launch_batch_f64in32_64(a, tiles, s);
+#define TSQR_CASE(NC) case NC: return tsqr::launch_batch_f64in32_##NC(a, tiles, s);
+    TSQR_FOR_EACH_NC(TSQR_CASE)
+#undef TSQR_CASE
     default: return hipErrorInvalidValue;
     }
 }
@@ -809,10 +842,9 @@ hipError_t dispatch_fallback(const tsqr::BatchArgs<double, float>& a, int tiles,
 hipError_t dispatch_mixed(const tsqr::MixedArgs& a, int nc, int batch, hipStream_t s)
 {
     switch (nc) {
-    case 16: return tsqr::launch_mixed_16(a, batch, s);
-    case 32: return tsqr::launch_mixed_32(a, batch, s);
-    case 50: return tsqr::launch_mixed_50(a, batch, s);
-    case 64: return tsqr::launch_mixed_64(a, batch, s);
+#define TSQR_CASE(NC) case NC: return tsqr::launch_mixed_##NC(a, batch, s);
+    TSQR_FOR_EACH_NC(TSQR_CASE)
+#undef TSQR_CASE
     default: return hipErrorInvalidValue;
     }
 }
@@ -820,9 +852,9 @@ hipError_t dispatch_mixed(const tsqr::MixedArgs& a, int nc, int batch, hipStream
 int gram_width(int nc)
 {
     switch (nc) {
-    case 16: return tsqr::MfmaGram<16>::W;
-    case 32: return tsqr::MfmaGram<32>::W;
-    case 50: return tsqr::MfmaGram<50>::W;
+#define TSQR_CASE(NC) case NC: return tsqr::MfmaGram<NC>::W;
+    TSQR_FOR_EACH_NC(TSQR_CASE)
+#undef TSQR_CASE
     default: return tsqr::MfmaGram<64>::W;
     }
 }
@@ -836,7 +868,7 @@ int mixed_plan_make(tsqr_handle_t h, int64_t batch, int64_t m, int64_t n, int64_
                     int64_t sample_rows, uint64_t seed, tsqr_mixed_plan_t* out)
 {
     if (n > TSQR_MAX_N) return TSQR_ERR_UNSUPPORTED;
-    const int nc = n > 0 ? padded_columns(n) : 16;
+    const int nc = n > 0 ? kernel_columns(n) : 16;
     if (nc < 0) return TSQR_ERR_UNSUPPORTED;
     int64_t srows = (sample_rows + tsqr::kSampleBlock - 1) / tsqr::kSampleBlock * tsqr::kSampleBlock;
     if (srows >= m) srows = 0;
@@ -853,7 +885,7 @@ int mixed_plan_make(tsqr_handle_t h, int64_t batch, int64_t m, int64_t n, int64_
     const int64_t sample_leaf = srows ? (batch * srows + 2047) / 2048 : 0;
     int rc = batch_plan_make(h, batch, n, ms.data(), offs.data(), ldas.data(), TSQR_F32, 0, &inner, sample_leaf);
     if (rc) return rc;
-    rc = batch_plan_make(h, batch, n, fms.data(), foffs.data(), fldas.data(), TSQR_F64, 8, &fb);
+    rc = batch_plan_make(h, batch, n, fms.data(), foffs.data(), fldas.data(), TSQR_F64, 8, &fb, 0, false);
     if (rc) {
         tsqr_batch_plan_destroy(inner);
         return rc;

@@ -123,12 +123,43 @@ __device__ __forceinline__ double fmadd(double a, double b, double c) { return _
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double absv(double x) { return __builtin_fabs(x); }
 __device__ __forceinline__ float absv(float x) { return __builtin_fabsf(x); }
-__device__ __forceinline__ double maxv(double a, double b) { return __builtin_fmax(a, b); }
-__device__ __forceinline__ float maxv(float a, float b) { return __builtin_fmaxf(a, b); }
-__device__ __forceinline__ double minv(double a, double b) { return __builtin_fmin(a, b); }
-__device__ __forceinline__ float minv(float a, float b) { return __builtin_fminf(a, b); }
-__device__ __forceinline__ double copysignv(double a, double b) { return __builtin_copysign(a, b); }
-__device__ __forceinline__ float copysignv(float a, float b) { return __builtin_copysignf(a, b); }
+// The hardware's maximum and minimum as they stand (a NaN gives the other
+// operand); the builtins quiet their operands first, one more instruction each.
+__device__ __forceinline__ double max_raw(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max_raw(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double min_raw(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "s"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float min_raw(float a, float b)
+{
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "s"(a), "v"(b));
+    return r;
+}
+// The sign bit of x in place, and a non-negative x with that sign
+__device__ __forceinline__ unsigned sign_of(double x) { return (unsigned)__double2hiint(x) & 0x80000000u; }
+__device__ __forceinline__ unsigned sign_of(float x) { return (unsigned)__float_as_int(x) & 0x80000000u; }
+__device__ __forceinline__ double with_sign(double x, unsigned s)
+{
+    return __hiloint2double((int)((unsigned)__double2hiint(x) ^ s), __double2loint(x));
+}
+__device__ __forceinline__ float with_sign(float x, unsigned s)
+{
+    return __int_as_float((int)((unsigned)__float_as_int(x) ^ s));
+}
 
 // Value of x held by the lane whose byte address (4 * lane) is src.
 __device__ __forceinline__ double bpermute(int src, double x)
@@ -615,13 +646,14 @@ __global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr
     leaf_tree_body<T, NC, RPL, WQ>(a, xcd_local_leaf(blockIdx.x, a.leaves), Rs, red);
 }
 
-// Rs := qr([Rs; R2]), both triangles packed in LDS
-template <typename T, int NC>
-__device__ __forceinline__ void merge_lds(const T* R2, T* Rs, T* work)
+// Rs := qr([Rs; R2]), both triangles packed in LDS: tree node id
+template <typename T, int NC, bool WQ>
+__device__ __forceinline__ void merge_lds(const LeafTreeArgs<T>& a, int id, const T* R2, T* Rs, T* work)
 {
     Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS> c;
     triangle_chunk<T, NC>(R2, c);
-    merge_panels<T, NC, false>(c, Rs, work, nullptr, nullptr);
+    merge_panels<T, NC, WQ>(c, Rs, work, WQ ? a.qs.Vn + (int64_t)id * Tri<NC>::kSize : nullptr,
+                            WQ ? a.qs.tau_node + (int64_t)id * NC : nullptr);
 }
 
 // Four leaves per workgroup, one wavefront each (one per SIMD of a compute
@@ -635,7 +667,7 @@ __device__ __forceinline__ void merge_lds(const T* R2, T* Rs, T* work)
 // workgroup past the last leaf only keep the barriers; with at most four leaves
 // no tree counter is touched.  Groups are numbered XCD-locally as single leaves
 // are.
-template <typename T, int NC, int RPL>
+template <typename T, int NC, int RPL, bool WQ = false>
 __global__ void __launch_bounds__(4 * kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_leaf_tree4_kernel(LeafTreeArgs<T> a)
 {
     __shared__ T Rs[4][Tri<NC>::kPadded];
@@ -643,11 +675,11 @@ __global__ void __launch_bounds__(4 * kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) 
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));   // uniform per wavefront
     const int base = 4 * xcd_local_leaf(blockIdx.x, (a.leaves + 3) / 4);
     const int leaf = base + w;
-    if (leaf < a.leaves) leaf_phase<T, NC, RPL>(a, leaf, Rs[w], red[w]);
+    if (leaf < a.leaves) leaf_phase<T, NC, RPL, WQ>(a, leaf, Rs[w], red[w]);
     __syncthreads();
     // level 0: leaf base + w (w even) takes base + w + 1 from below
     if ((w & 1) == 0) {
-        if (leaf + 1 < a.leaves) merge_lds<T, NC>(Rs[w + 1], Rs[w], red[w]);
+        if (leaf + 1 < a.leaves) merge_lds<T, NC, WQ>(a, leaf, Rs[w + 1], Rs[w], red[w]);
     } else if (a.stamps && leaf < a.leaves && lane_id() == 0) {
         a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
         a.stamps[4 * leaf + 3] = 0;
@@ -655,8 +687,8 @@ __global__ void __launch_bounds__(4 * kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) 
     __syncthreads();
     // level 1: base takes base + 2, then the tree goes on through memory
     if (w == 0) {
-        if (base + 2 < a.leaves) merge_lds<T, NC>(Rs[2], Rs[0], red[0]);
-        tree_phase<T, NC>(a, leaf, base, 2, Rs[0], red[0]);
+        if (base + 2 < a.leaves) merge_lds<T, NC, WQ>(a, base + 1, Rs[2], Rs[0], red[0]);
+        tree_phase<T, NC, WQ>(a, leaf, base, 2, Rs[0], red[0]);
     } else if (w == 2 && a.stamps && leaf < a.leaves && lane_id() == 0) {
         a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
         a.stamps[4 * leaf + 3] = 1;

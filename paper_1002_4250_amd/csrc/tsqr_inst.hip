@@ -78,8 +78,12 @@ hipError_t TSQR_IN32_FN2(TSQR_INST_NC)(const BatchArgs<double, float>& a, int ti
 hipError_t TSQR_QR_FN2(qr_leaf_tree, TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)(
     const LeafTreeArgs<TSQR_INST_TAG>& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((dev::tsqr_leaf_tree_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL, true>),
-                       dim3(a.leaves), dim3(dev::kWave), 0, s, a);
+    if (a.leaves > 1)
+        hipLaunchKernelGGL((dev::tsqr_leaf_tree4_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL, true>),
+                           dim3((a.leaves + 3) / 4), dim3(4 * dev::kWave), 0, s, a);
+    else
+        hipLaunchKernelGGL((dev::tsqr_leaf_tree_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL, true>),
+                           dim3(a.leaves), dim3(dev::kWave), 0, s, a);
     return hipGetLastError();
 }
 hipError_t TSQR_QR_FN2(q_tree, TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)(const LeafTreeArgs<TSQR_INST_TAG>& a,

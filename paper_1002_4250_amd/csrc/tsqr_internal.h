@@ -18,7 +18,7 @@ struct QStore {
     T* tau_leaf;          // (global chunk index) x NC
     T* Vn;                // per tree node (counter id): packed NC x NC triangle, the R2 part of its reflectors
     T* tau_node;          // per tree node: NC
-    T* qblk;              // per leaf: NC x NC column-major block of Q (output of the tree pass)
+    T* qblk;              // per leaf: NC x NC block of Q, by rows (output of the tree pass)
 };
 
 // T is the arithmetic type; TIn the storage type of A (FP32 storage factored
@@ -88,10 +88,7 @@ TSQR_OP_INSTANCES(TSQR_DECLARE_OP)
 // one per column count at 8 rows per lane
 #define TSQR_DECLARE_BATCH_IN32(NC) \
     hipError_t launch_batch_f64in32_##NC(const BatchArgs<double, float>& a, int tiles, hipStream_t s);
-TSQR_DECLARE_BATCH_IN32(16)
-TSQR_DECLARE_BATCH_IN32(32)
-TSQR_DECLARE_BATCH_IN32(50)
-TSQR_DECLARE_BATCH_IN32(64)
+TSQR_FOR_EACH_NC(TSQR_DECLARE_BATCH_IN32)
 #undef TSQR_DECLARE_BATCH_IN32
 #undef TSQR_DECLARE_LEAF
 #undef TSQR_DECLARE_BATCH
@@ -143,7 +140,7 @@ hipError_t launch_surrogate_apply(const float* Rt, const float* Y, int batch, in
 hipError_t launch_fill_u32(unsigned* p, int64_t count, unsigned value, hipStream_t s);
 
 // Applying Q^T from the stored reflectors: B (m x k, column-major, ldb), the
-// per-leaf NC x kQtCols blocks tq (column-major, ld NC), the output C (n x k,
+// per-leaf NC x kQtCols blocks tq (by rows), the output C (n x k,
 // ldc).
 constexpr int kQtCols = 64;
 template <typename T>
@@ -197,10 +194,7 @@ struct MixedArgs {
 };
 
 #define TSQR_DECLARE_MIXED(NC) hipError_t launch_mixed_##NC(const MixedArgs& a, int batch, hipStream_t s);
-TSQR_DECLARE_MIXED(16)
-TSQR_DECLARE_MIXED(32)
-TSQR_DECLARE_MIXED(50)
-TSQR_DECLARE_MIXED(64)
+TSQR_FOR_EACH_NC(TSQR_DECLARE_MIXED)
 #undef TSQR_DECLARE_MIXED
 
 }  // namespace tsqr

@@ -289,16 +289,13 @@ __device__ __forceinline__ void panel_products(const Chunk<float, RB, NX>& x, co
 // the column in front of which the panel was cut.
 //
 // With y = 1/sqrt(alpha^2 + sigma^2), z = |alpha| y and q = 1/(1 + z):
-//     tau = 1 + z,  s = sgn y q,  tau s = sgn y,  R(j, :) - tau w = -(z R(j, :) + sgn y d),
+//     tau = 1 + z,  s = sgn y q,  tau s = sgn y,  R(j, :) - tau w = -(z R(j, :) + sgn y d).
+// The diagonal entry takes the norm itself, S y with one Newton correction:
+// the last formula's three roundings there would dominate the error of an R
+// whose diagonal is its largest part (FP32, 2^22 x 50 uniform: 7.0e-8 relative
+// against 5.5e-8).
 // y and q from the hardware estimates (about 2^-24 on gfx950 in FP64, 1 ulp in
 // FP32) by one third-order step each, which leaves 2^-72 (FP32: second-order).
-template <typename T>
-__device__ __forceinline__ T refined_rsq(T S)
-{
-    const T y = hw_rsq(S);
-    const T e = fmadd(-S * y, y, T(1));
-    return fmadd(y * e, sizeof(T) == 8 ? fmadd(e, T(0.375), T(0.5)) : T(0.5), y);
-}
 template <typename T>
 __device__ __forceinline__ T refined_rcp(T u)
 {
@@ -307,21 +304,29 @@ __device__ __forceinline__ T refined_rcp(T u)
     return fmadd(q, sizeof(T) == 8 ? fmadd(e, e, e) : e, q);
 }
 
-// The scalars of one reflector: z, q and sgn y (see above).  S = 0 (a zero
-// column below a zero alpha) gives z = 0 and finite y, q.
+// The scalars of one reflector: z, q, sgn y (see above) and beta.  An S below
+// the smallest normal number (rounding can leave it negative) still gives
+// finite z, q and y; S = 0, a zero column below a zero alpha, gives z = 0.
 template <typename T>
 struct PanelScalars {
-    T z, q, sy;
+    T z, q, sy, beta;
 };
 template <typename T>
 __device__ __forceinline__ PanelScalars<T> panel_scalars(T alpha, T S)
 {
 #pragma clang fp contract(off)
     PanelScalars<T> h;
-    const T y = refined_rsq(maxv(S, Limits<T>::tiny));
+    const T St = max_raw(S, Limits<T>::tiny);
+    const T y0 = hw_rsq(St);
+    const T t = St * y0;
+    const T e = fmadd(-t, y0, T(1));
+    const T c = e * (sizeof(T) == 8 ? fmadd(e, T(0.375), T(0.5)) : T(0.5));
+    const T y = fmadd(y0, c, y0);
     h.z = absv(alpha) * y;
     h.q = refined_rcp(T(1) + h.z);
-    h.sy = copysignv(y, alpha);
+    h.sy = with_sign(y, sign_of(alpha));
+    const T nrm = St * y;
+    h.beta = with_sign(fmadd(T(0.5) * y, fmadd(-nrm, nrm, St), nrm), sign_of(alpha) ^ 0x80000000u);
     return h;
 }
 
@@ -334,7 +339,7 @@ __device__ __forceinline__ void panel_apply(const PanelScalars<T>& h, T sigma2, 
 {
 #pragma clang fp contract(off)
     const T w = fmadd(h.sy * h.q, g[j], r[j]);
-    r[j] = fmadd(-h.z, r[j], -h.sy * g[j]);
+    r[j] = lane == J0 + j ? h.beta : fmadd(-h.z, r[j], -h.sy * g[j]);
     nf[j] = -h.sy * w;
     if constexpr (Mask) nf[j] = lane > J0 + j ? nf[j] : T(0);
     if constexpr (j + 1 < NJ) {
@@ -364,8 +369,8 @@ __device__ __forceinline__ void panel_coefficients(T (&nf)[4], const T (&n)[4][4
 // the panel has to be cut (growth) or a column calls for an identity reflector
 // (one whose sum of squares is below the smallest normal number; a zero
 // column below a zero alpha does no harm here).
-template <typename T, int NC, int P>
-__device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4])
+template <typename T, int NC, int P, bool WQ>
+__device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4], int lane)
 {
     constexpr int J0 = 4 * P;
     constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
@@ -373,25 +378,30 @@ __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4
     T grow = T(0), least = T(0);
     uint64_t over = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) nf[j] = T(0);
+    for (int j = 0; j < 4; ++j) nf[j] = tau[j] = s[j] = T(0);
     static_for<0, NJ>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         alpha[j] = lane_value(r[j], J0 + j);
         sigma2[j] = lane_value(g[j], J0 + j);
         const T S = fmadd(alpha[j], alpha[j], sigma2[j]);
-        least = j == 0 ? sigma2[j] : minv(sigma2[j], least);
+        least = j == 0 ? sigma2[j] : min_raw(sigma2[j], least);
         if constexpr (j > 0)
             over |= __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) & ((uint64_t)1 << (J0 + j));
         const PanelScalars<T> h = panel_scalars(alpha[j], S);
-        panel_apply<T, J0, NJ, j, false>(h, sigma2[j], g, r, nf, n, grow, 0);
+        s[j] = h.sy * h.q;
+        tau[j] = T(1) + h.z;
+        panel_apply<T, J0, NJ, j, WQ>(h, sigma2[j], g, r, nf, n, grow, lane);
     });
     panel_coefficients<T, NJ>(nf, n);
     bool good = over == 0;
     if (__builtin_amdgcn_ballot_w64(least < Limits<T>::tiny) != 0) [[unlikely]] {
+        if constexpr (WQ) good = false;   // a stored reflector has to be the identity
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            if (__builtin_amdgcn_ballot_w64(sigma2[j] < Limits<T>::tiny && (sigma2[j] > T(0) || alpha[j] != T(0))) != 0)
-                good = false;
+            if (__builtin_amdgcn_ballot_w64(sigma2[j] < Limits<T>::tiny) != 0) {
+                if (__builtin_amdgcn_ballot_w64(sigma2[j] != T(0) || alpha[j] != T(0)) != 0) good = false;
+                r[j] = lane == J0 + j ? alpha[j] : r[j];
+            }
     }
     return good;
 }
@@ -424,6 +434,7 @@ __device__ __forceinline__ int panel_reflectors_cut(T (&g)[4], T (&r)[4], T (&nf
         if (__builtin_amdgcn_ballot_w64(sigma2 >= Limits<T>::tiny) == 0 || j < lo || j >= hi) [[unlikely]] {
             h.z = T(-1);                  // an identity reflector
             h.sy = T(0);
+            h.beta = alpha;
         }
         s[j] = h.sy * h.q;
         tau[j] = T(1) + h.z;
@@ -569,7 +580,7 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
     const int lane = lane_id();
     T* Rl = Rs + lane;
     // lo < 0: all reflectors at once; otherwise from column lo on, with cuts
-    int lo = WQ ? 0 : -1, hi;
+    int lo = -1, hi;
     do {
         // rows J0.. of R, one column per lane (lanes left of the diagonal and
         // past NC read other entries of the padded triangle; nothing uses them)
@@ -580,21 +591,21 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
         lds_order();
         panel_products<P, P, NS, RA>(c, c, g);
         hi = NJ;
-        if (!WQ && lo < 0) {
-            if (!panel_reflectors<T, NC, P>(g, r, nf)) [[unlikely]] {
+        // (the lane passes through an opaque copy so that the compiler does not
+        // keep the masks of every panel alive over the whole chunk)
+        int col = lane;
+        asm volatile("" : "+v"(col));
+        if (lo < 0) {
+            if (!panel_reflectors<T, NC, P, WQ>(g, r, nf, tau, s, col)) [[unlikely]] {
                 lo = 0;
                 hi = 0;
                 continue;
             }
         } else {
-            hi = panel_reflectors_cut<T, NC, P, WQ>(g, r, nf, tau, s, lane, lo);
+            hi = panel_reflectors_cut<T, NC, P, WQ>(g, r, nf, tau, s, col, lo);
         }
         // last row first: a lane left of a row's diagonal writes into the end of
-        // the row before, which the next store writes again.  (The lane passes
-        // through an opaque copy so that the compiler does not keep one mask per
-        // panel alive over the whole chunk.)
-        int col = lane;
-        asm volatile("" : "+v"(col));
+        // the row before, which the next store writes again.
         if ((unsigned)(col - J0) < (unsigned)(NC - J0)) {
 #pragma unroll
             for (int j = NJ - 1; j >= 0; --j) {
@@ -607,7 +618,7 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
         const Update up(c, P, work, lane);
         static_for<P + 1, NS>([&](auto sc) { up.apply(c, decltype(sc)::value); });
         mfma_settle();
-        if constexpr (WQ) up.reflectors(P, lane, s, [&](int rb, T v) { keep(rb, v, tau, lo, hi); });
+        if constexpr (WQ) up.reflectors(P, lane, s, [&](int rb, T v) { keep(rb, v, tau, lo < 0 ? 0 : lo, hi); });
         if (hi < NJ) [[unlikely]] {
             up.apply_from(c, P, lane, hi);
             mfma_settle();
