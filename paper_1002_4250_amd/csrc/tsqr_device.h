@@ -423,10 +423,24 @@ namespace dev {
 
 // ---- the fused leaf + tree kernel --------------------------------------------
 
-// One chunk of a leaf: the panels in order, each followed (with PF) by the
-// loads of the next chunk's columns into its registers, which no later panel
-// reads.
-template <typename T, int NC, int RPL, bool WQ, bool PF, typename TIn>
+// Copy a packed triangle from LDS to global memory, the reads first
+template <typename T, int NC>
+__device__ __forceinline__ void triangle_to_global(const T* src, T* __restrict__ dst)
+{
+    constexpr int NT = Tri<NC>::kSize;
+    constexpr int U = (NT + kWave - 1) / kWave;
+    const int lane = lane_id();
+    T t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = src[lane + u * kWave < NT ? lane + u * kWave : 0];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (lane + u * kWave < NT) dst[lane + u * kWave] = t[u];
+}
+
+// One chunk of a leaf: the panels in order, each followed by the loads of the
+// next chunk's columns into its registers, which no later panel reads.
+template <typename T, int NC, int RPL, bool WQ, typename TIn>
 __device__ __forceinline__ void leaf_chunk(Chunk<T, RPL, Slots<NC>::NS>& c, T* Rs, T* work, int q, int p,
                                            Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
 {
@@ -439,7 +453,7 @@ __device__ __forceinline__ void leaf_chunk(Chunk<T, RPL, Slots<NC>::NS>& c, T* R
                 if (rb == 0 && lane_id() == 0)
                     for (int j = lo; j < hi; ++j) vs.tau[4 * P + j] = tau[j];
             });
-        if constexpr (PF) prefetch_slot<T, RPL, TIn>(c, P, pf);
+        prefetch_slot<T, RPL, TIn>(c, P, pf);
     });
 }
 
@@ -468,7 +482,7 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
     const int64_t r1 = (r0 + a.leaf_rows < a.m) ? r0 + a.leaf_rows : a.m;
     const uint64_t t_start = a.stamps ? (uint64_t)wall_clock64() : 0;
 
-    for (int i = lane; i < NT; i += kWave) Rs[i] = T(0);
+    for (int i = lane; i < Tri<NC>::kPadded; i += kWave) Rs[i] = T(0);
 
     // step 1 of the method: the local factorisation of rows [r0, r1)
     if (r1 > r0) {
@@ -498,15 +512,18 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
                     c.put(r, s, (ok && k < a.n) ? (T)a.A[row + (int64_t)k * a.lda] : T(0));
                 }
             }
-            for (; t + 1 < nfull; ++t) {
-                Prefetch<T, RPL, TIn> pf = make_prefetch<T, RPL, TIn>(a.A, a.lda, a.n, r0 + (t + 1) * CH, q, p);
+            // (where no full chunk follows, the prefetch reads the block of zeros: a
+            // second copy of the chunk's code without it would cost more to fetch
+            // than these loads)
+            bool more;
+            do {
+                more = t + 1 < nfull;
+                Prefetch<T, RPL, TIn> pf = make_prefetch<T, RPL, TIn>(
+                    a.A, a.lda, more ? a.n : 0, more ? r0 + (t + 1) * CH : 0, q, p);
                 sink(t);
-                leaf_chunk<T, NC, RPL, WQ, true, TIn>(c, Rs, red, q, p, pf, vs);
-            }
-            Prefetch<T, RPL, TIn> none{};
-            sink(t);
-            leaf_chunk<T, NC, RPL, WQ, false, TIn>(c, Rs, red, q, p, none, vs);
-            ++t;
+                leaf_chunk<T, NC, RPL, WQ, TIn>(c, Rs, red, q, p, pf, vs);
+                ++t;
+            } while (more);
         }
     }
     wave_sync();
@@ -531,10 +548,7 @@ __device__ __forceinline__ void tree_phase(const LeafTreeArgs<T, TIn>& a, int le
     int node = node0;
     int level = level0;
     bool root = ((1 << level) >= P);
-    if (!root) {
-        T* slot = a.tri + (int64_t)node * NT;
-        for (int i = lane; i < NT; i += kWave) slot[i] = Rs[i];
-    }
+    if (!root) triangle_to_global<T, NC>(Rs, a.tri + (int64_t)node * NT);
     while (!root) {
         const int span = 1 << level;
         const bool is_left = (node & (2 * span - 1)) == 0;
@@ -577,22 +591,27 @@ __device__ __forceinline__ void tree_phase(const LeafTreeArgs<T, TIn>& a, int le
         node = left;
         ++level;
         root = ((1 << level) >= P);
-        if (!root) {
-            T* slot = a.tri + (int64_t)node * NT;
-            for (int i = lane; i < NT; i += kWave) slot[i] = Rs[i];
-        }
+        if (!root) triangle_to_global<T, NC>(Rs, a.tri + (int64_t)node * NT);
     }
 
     // root: positive diagonal, +0 below it, leading n-by-n block only
+    // (lane i holds row i, eight columns in flight)
     const int n = a.n;
-    for (int idx = lane; idx < n * n; idx += kWave) {
-        const int i = idx % n, k = idx / n;
-        T v = T(0);
-        if (k >= i) {
-            v = Rs[Tri<NC>::off(i) + (k - i)];
-            if (__builtin_signbit(Rs[Tri<NC>::off(i)])) v = -v;
+    {
+        const int i = lane < n ? lane : 0;
+        const T* row = Rs + Tri<NC>::off(i) - i;
+        const bool flip = __builtin_signbit(row[i]);
+        for (int k0 = 0; k0 < n; k0 += 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = row[k0 + u];      // past the row's end: inside the padding
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u;
+                const T x = k < i ? T(0) : (flip ? -v[u] : v[u]);
+                if (lane < n && k < n) a.R[i + (int64_t)k * a.ldr] = x;
+            }
         }
-        a.R[i + (int64_t)k * a.ldr] = v;
     }
     if (a.stamps && lane == 0) {
         a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();

@@ -281,8 +281,9 @@ __device__ __forceinline__ void panel_products(const Chunk<float, RB, NX>& x, co
     }
 }
 
-// The reflectors of a panel (step 2), one column of [R; C] per lane: g[j] are
-// the inner products of X(:, j) with the lane's column, r[j] row 4P + j of R.
+// The reflectors of a panel (step 2), one column of [R; C] per lane, the panel's
+// own NJ columns in the lanes from J0 on: g[j] are the inner products of X(:, j)
+// with the lane's column, r[j] the panel's row j of R.
 // Columns below lo are done already.  On return r holds the new rows, nf the
 // coefficients -F in terms of the columns of X (zero for columns outside
 // [lo, hi)), tau and s the reflectors' scalars, and the result is hi: NJ, or
@@ -369,11 +370,9 @@ __device__ __forceinline__ void panel_coefficients(T (&nf)[4], const T (&n)[4][4
 // the panel has to be cut (growth) or a column calls for an identity reflector
 // (one whose sum of squares is below the smallest normal number; a zero
 // column below a zero alpha does no harm here).
-template <typename T, int NC, int P, bool WQ>
+template <typename T, int J0, int NJ, bool WQ>
 __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4], int lane)
 {
-    constexpr int J0 = 4 * P;
-    constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
     T n[4][4], alpha[4], sigma2[4];
     T grow = T(0), least = T(0);
     uint64_t over = 0;
@@ -410,12 +409,10 @@ __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4
 // front of the first column (after lo) whose growth is over the limit, and the
 // result is that column, or NJ.  nf is zero for columns outside [lo, hi); in the
 // lanes of columns left of hi it is valid with WQ only.
-template <typename T, int NC, int P, bool WQ>
+template <typename T, int J0, int NJ, bool WQ>
 __device__ __forceinline__ int panel_reflectors_cut(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4],
                                                     int lane, int lo)
 {
-    constexpr int J0 = 4 * P;
-    constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
     T n[4][4];
     T grow = T(0);
     int hi = NJ;
@@ -480,6 +477,14 @@ struct PanelUpdate<double, RA> {
 #pragma unroll
         for (int rb = 0; rb < RA; ++rb) c.v[rb][s] = mfma4(xt[rb], f, c.v[rb][s]);
     }
+    // the columns of slot s, moved to slot s - 1
+    template <typename C>
+    __device__ __forceinline__ void apply_shift(C& c, int s) const
+    {
+        const double f = fr[4 * s];
+#pragma unroll
+        for (int rb = 0; rb < RA; ++rb) c.v[rb][s - 1] = mfma4(xt[rb], f, c.v[rb][s]);
+    }
     // the panel's own columns from column hi on
     template <typename C>
     __device__ __forceinline__ void apply_from(C& c, int s, int lane, int hi) const
@@ -534,6 +539,17 @@ struct PanelUpdate<float, RA> {
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int r = 0; r < RV; ++r) c.v[r][s] = mfma4((float)xt[r][k], (float)f[k], c.v[r][s]);
+    }
+    template <typename C>
+    __device__ __forceinline__ void apply_shift(C& c, int s) const
+    {
+        const float4v f = fr[4 * s];
+#pragma unroll
+        for (int r = 0; r < RV; ++r) c.v[r][s - 1] = mfma4((float)xt[r][0], (float)f[0], c.v[r][s]);
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+#pragma unroll
+            for (int r = 0; r < RV; ++r) c.v[r][s - 1] = mfma4((float)xt[r][k], (float)f[k], c.v[r][s - 1]);
     }
     template <typename C>
     __device__ __forceinline__ void apply_from(C& c, int s, int lane, int hi) const
@@ -596,13 +612,13 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
         int col = lane;
         asm volatile("" : "+v"(col));
         if (lo < 0) {
-            if (!panel_reflectors<T, NC, P, WQ>(g, r, nf, tau, s, col)) [[unlikely]] {
+            if (!panel_reflectors<T, J0, NJ, WQ>(g, r, nf, tau, s, col)) [[unlikely]] {
                 lo = 0;
                 hi = 0;
                 continue;
             }
         } else {
-            hi = panel_reflectors_cut<T, NC, P, WQ>(g, r, nf, tau, s, col, lo);
+            hi = panel_reflectors_cut<T, J0, NJ, WQ>(g, r, nf, tau, s, col, lo);
         }
         // last row first: a lane left of a row's diagonal writes into the end of
         // the row before, which the next store writes again.
@@ -628,27 +644,108 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
     } while (hi < NJ);
 }
 
-// R := qr([R; R2]), R packed in LDS, the triangle R2 in c (zero below its
-// diagonal): the operator of section 2 in the structured form of Table 3 (a
-// panel touches only the row blocks of R2 that reach its columns).  With WQ the
-// reflectors' R2 parts go to Vn (packed by rows) and their tau to tau_out.
+// ---- the operator on two triangles ---------------------------------------------
+//
+// R := qr([R; R2]), R packed in LDS, R2 in registers: the operator of section 2 in
+// the structured form of Table 3 (a panel touches only the row blocks of R2 that
+// reach its columns).  A merge runs its code once or a few times, so the fetch of
+// instructions that are in no cache yet counts: fully unrolled (40 KB), a merge
+// that a kernel ran for the first time took about twice its warm 14 us.  The
+// panels of a row block K (four of them) therefore share one loop body: the
+// current panel is always slot 0 and the lanes 0..3, every update moves its slot
+// down by one (the matrix instruction writes where it likes), and the slots that
+// run out at the end, at most three, are updated for nothing.
+
+// Slot s of row block rb holds column block s + first(rb) when the merge begins.
+// FP64 keeps the nonzero part only; the FP32 accumulator holds the four row blocks
+// together.
+template <typename T>
+__device__ __forceinline__ constexpr int merge_first(int rb)
+{
+    return sizeof(T) == 8 ? 4 * rb : 0;
+}
+
+// The panels 4 K .. of row block K.  With WQ the reflectors' R2 parts go to Vn
+// (packed by rows) and their tau to tau_out.
+template <typename T, int NC, int K, bool WQ>
+__device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work, T* Vn,
+                                                T* tau_out)
+{
+    constexpr int NS = Slots<NC>::NS;
+    constexpr int S = NS - 4 * K;                  // live slots at the start
+    constexpr int RA = K + 1;
+    using Update = PanelUpdate<T, RA>;
+    const int lane = lane_id();
+    const int q = c.q(lane), p = c.p(lane);
+    T* Rl = Rs + lane;
+#pragma nounroll
+    for (int P = 4 * K; P < (S < 4 ? NS : 4 * K + 4); ++P) {
+        const int J0 = 4 * P;
+        // offset of entry (J0 + j, J0 + lane) of the packed triangle, without the lane
+        int at[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) at[j] = __builtin_amdgcn_readfirstlane(Tri<NC>::off(J0 + j) - j);
+        int lo = -1, hi;
+        do {
+            T r[4], g[4], nf[4], tau[4], s[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = Rl[at[j]];
+            if constexpr (NC % 4 != 0) {
+                // the columns past NC of the last slot stay zero
+#pragma unroll
+                for (int j = 0; j < 4; ++j) r[j] = lane < NC - J0 && J0 + j < NC ? r[j] : T(0);
+            }
+            Update::stage(c, 0, work, lane);
+            lds_order();
+            panel_products<0, 0, S, RA>(c, c, g);
+            hi = 4;
+            if (lo < 0) {
+                if (!panel_reflectors<T, 0, 4, WQ>(g, r, nf, tau, s, lane)) [[unlikely]] {
+                    lo = 0;
+                    hi = 0;
+                    continue;
+                }
+            } else {
+                hi = panel_reflectors_cut<T, 0, 4, WQ>(g, r, nf, tau, s, lane, lo);
+            }
+            // last row first, as in panel_step
+            if (lane < NC - J0) {
+#pragma unroll
+                for (int j = 3; j >= 0; --j) {
+                    if (NC % 4 == 0 || j < NC % 4 || J0 + j < NC) Rl[at[j]] = r[j];
+                    asm volatile("" ::: "memory");
+                }
+            }
+            Update::put_f(work, lane, nf);
+            lds_order();
+            const Update up(c, 0, work, lane);
+            if constexpr (WQ) {
+                up.reflectors(0, lane, s, [&](int rb, T v) {
+                    const int i = 16 * rb + p, k = J0 + q;
+                    if (i <= k && k < NC && q >= lo && q < hi) Vn[Tri<NC>::off(i) + k - i] = v;
+                });
+                if (lane < 4 && lane >= lo && lane < hi && J0 + lane < NC)
+                    tau_out[J0 + lane] = lane == 0 ? tau[0] : lane == 1 ? tau[1] : lane == 2 ? tau[2] : tau[3];
+            }
+            if (hi < 4) [[unlikely]] {
+                static_for<1, S>([&](auto sc) { up.apply(c, decltype(sc)::value); });
+                up.apply_from(c, 0, lane, hi);
+            } else {
+                static_for<1, S>([&](auto sc) { up.apply_shift(c, decltype(sc)::value); });
+            }
+            mfma_settle();
+            lds_order();
+            lo = hi;
+        } while (hi < 4);
+    }
+}
+
 template <typename T, int NC, bool WQ>
 __device__ __forceinline__ void merge_panels(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work, T* Vn,
                                              T* tau_out)
 {
-    constexpr int RB = MergeRows<T, NC>::RB;
-    constexpr int NS = Slots<NC>::NS;
-    const int lane = lane_id();
-    const int q = c.q(lane), p = c.p(lane);
-    static_for<0, NS>([&](auto pc) {
-        constexpr int P = decltype(pc)::value;
-        panel_step<T, NC, RB, P / 4 + 1, P, WQ>(c, Rs, work, [&](int rb, T v, const T(&tau)[4], int lo, int hi) {
-            const int i = 16 * rb + p, k = 4 * P + q;
-            if (i <= k && k < NC && q >= lo && q < hi) Vn[Tri<NC>::off(i) + k - i] = v;
-            if (rb == 0 && lane == 0)
-                for (int j = lo; j < hi; ++j) tau_out[4 * P + j] = tau[j];
-        });
-    });
+    static_for<0, (Slots<NC>::NS + 3) / 4>(
+        [&](auto kc) { merge_row_block<T, NC, decltype(kc)::value, WQ>(c, Rs, work, Vn, tau_out); });
 }
 
 // The triangle tri (packed by rows, LDS or global) as the bottom operand of
@@ -656,6 +753,7 @@ __device__ __forceinline__ void merge_panels(Chunk<T, MergeRows<T, NC>::RB, Slot
 template <typename T, int NC>
 __device__ __forceinline__ void triangle_chunk(const T* tri, Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c)
 {
+    constexpr int NS = Slots<NC>::NS;
     const int lane = lane_id();
     const int q = c.q(lane), p = c.p(lane);
 #pragma unroll
@@ -663,11 +761,11 @@ __device__ __forceinline__ void triangle_chunk(const T* tri, Chunk<T, MergeRows<
         const int i = 16 * rb + p;
         const int base = Tri<NC>::off(i) - i + q;       // entry (i, 4 s + q) is at base + 4 s
 #pragma unroll
-        for (int s = 0; s < Slots<NC>::NS; ++s) {
-            const int k = 4 * s + q;
+        for (int s = 0; s < NS; ++s) {
+            const int b = s + merge_first<T>(rb), k = 4 * b + q;
             const bool in = i <= k && k < NC;
-            const T t = 4 * s + 3 < 16 * rb ? T(0) : tri[in ? base + 4 * s : 0];
-            c.put(rb, s, in ? t : T(0));
+            const T t = (b >= NS || 4 * b + 3 < 16 * rb) ? T(0) : tri[in ? base + 4 * b : 0];
+            c.put(rb, s, in && b < NS ? t : T(0));
         }
     }
 }

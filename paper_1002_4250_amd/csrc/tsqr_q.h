@@ -36,6 +36,36 @@ namespace dev {
 constexpr int kTopStride = kWave;      // row J of a top block at J * kTopStride, one column per lane
 // (the blocks in the workspace lie by rows as well: qblk NC x NC, tq NC x kQtCols)
 
+// Rows of kCols columns (leading dimension ld, lanes past them zero) from global
+// memory to a top block: all loads first, so they are in flight together
+template <typename T, int NC, int kCols, int kLd>
+__device__ __forceinline__ void load_top(const T* __restrict__ src, T* top)
+{
+    const int lane = lane_id();
+    T t[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) t[j] = src[j * kLd + (lane < kCols ? lane : 0)];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) top[j * kTopStride + lane] = lane < kCols ? t[j] : T(0);
+}
+template <typename T, int NC, int kCols, int kLd>
+__device__ __forceinline__ void store_top(const T* top, T* __restrict__ dst)
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+        const T t = top[j * kTopStride + lane];
+        if (lane < kCols) dst[j * kLd + lane] = t;
+    }
+}
+
+// the rows of the last panel past NC
+template <typename T, int NC>
+__device__ __forceinline__ void zero_spare_rows(T* top)
+{
+    for (int j = NC; j < 4 * Slots<NC>::NS; ++j) top[j * kTopStride + lane_id()] = T(0);
+}
+
 // v_i . v_j of the panel's columns: entry (i, j) is read from one lane
 template <int RA, int RB>
 __device__ __forceinline__ void panel_gram(const Chunk<double, RB, 1>& x, double (&v)[4])
@@ -66,15 +96,18 @@ __device__ __forceinline__ void panel_gram(const Chunk<float, RB, 1>& x, float (
 }
 __device__ __forceinline__ float gram_entry(const float (&v)[4], int i, int j) { return lane_value(v[i], j); }
 
-// The four reflectors of panel P, X in x (its first RA row blocks), applied to
+// The four reflectors from column J0 on, X in x (its first RA row blocks), applied to
 // the stack [T; C]: T in LDS (rows of kTopStride), C the KS slots of c.  Forward:
-// H_0 first (Q^T); otherwise H_3 first (Q).  With Zero, C is zero on entry.
-// Lane J of taus holds tau_J.  Lanes past 4 KS compute on a spare column of T.
-template <typename T, int NC, int RB, int RA, int P, int KS, bool Forward, bool Zero>
-__device__ __forceinline__ void apply_panel(const Chunk<T, RB, 1>& x, Chunk<T, RB, KS>& c, T* top, T* work, T taus)
+// H_0 first (Q^T); otherwise H_3 first (Q).  Lane J of taus holds tau_J (zero past
+// the last reflector).  Lanes past 4 KS compute on a spare column of T.  One loop
+// body serves every panel: the passes over the tree run it a dozen times per
+// launch, and unrolled their time was mostly the fetch of instructions (34 us per
+// level at n = 50, FP64).
+template <typename T, int RB, int RA, int KS, bool Forward>
+__device__ __forceinline__ void apply_panel(int J0, const Chunk<T, RB, 1>& x, Chunk<T, RB, KS>& c, T* top, T* work,
+                                            T taus)
 {
-    constexpr int J0 = 4 * P;
-    constexpr int NJ = NC - J0 < 4 ? NC - J0 : 4;
+    constexpr int NJ = 4;
     using Update = PanelUpdate<T, RA>;
     const int lane = lane_id();
     T t[4], g[4], v[4], y[4] = {T(0), T(0), T(0), T(0)};
@@ -84,10 +117,10 @@ __device__ __forceinline__ void apply_panel(const Chunk<T, RB, 1>& x, Chunk<T, R
     Update::stage(x, 0, work, lane);
     lds_order();
     panel_gram<RA>(x, v);
-    if constexpr (!Zero) panel_products<0, 0, KS, RA>(x, c, g);
+    panel_products<0, 0, KS, RA>(x, c, g);
     T w[4];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) w[j] = Zero ? t[j] : t[j] + g[j];
+    for (int j = 0; j < NJ; ++j) w[j] = t[j] + g[j];
     static_for<0, NJ>([&](auto jc) {
         constexpr int j = Forward ? decltype(jc)::value : NJ - 1 - decltype(jc)::value;
         y[j] = lane_value(taus, J0 + j) * w[j];
@@ -120,16 +153,38 @@ __device__ __forceinline__ void load_reflectors(Chunk<T, RPL, 1>& x, const T* V,
 }
 
 // The merge's reflectors, panel P: rows of the packed triangle in LDS
-template <typename T, int NC, int P, int RB>
-__device__ __forceinline__ void node_reflectors(Chunk<T, RB, 1>& x, const T* Vl, int q, int p)
+template <typename T, int NC, int RB>
+__device__ __forceinline__ void node_reflectors(Chunk<T, RB, 1>& x, const T* Vl, int P, int q, int p)
 {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int i = 16 * rb + p, k = 4 * P + q;
-        const bool in = rb <= P / 4 && i <= k && k < NC;
+        const bool in = i <= k && k < NC;
         const T t = Vl[in ? Tri<NC>::off(i) + k - i : 0];
         x.put(rb, 0, in ? t : T(0));
     }
+}
+
+// All reflectors of a merge applied to [T; C].  The panels of the first two row
+// blocks leave the other rows alone.
+template <typename T, int NC, int KS, bool Forward>
+__device__ __forceinline__ void apply_node(Chunk<T, MergeRows<T, NC>::RB, KS>& c, const T* Vl, T* top, T* work, T tau,
+                                           int q, int p)
+{
+    constexpr int RB = MergeRows<T, NC>::RB, NS = Slots<NC>::NS;
+    constexpr int RL = RB < 2 ? RB : 2, PL = NS < 8 ? NS : 8;
+    auto part = [&](auto rows, int first, int last) {
+#pragma nounroll
+        for (int i = first; i < last; ++i) {
+            const int P = Forward ? i : first + last - 1 - i;
+            Chunk<T, RB, 1> x;
+            node_reflectors<T, NC>(x, Vl, P, q, p);
+            apply_panel<T, RB, decltype(rows)::value, KS, Forward>(4 * P, x, c, top, work, tau);
+        }
+    };
+    if constexpr (!Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, NS);
+    part(std::integral_constant<int, RL>{}, 0, PL);
+    if constexpr (Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, NS);
 }
 
 // Level `level` of the tree, root first: workgroup g takes the merge whose
@@ -141,7 +196,7 @@ __global__ void __launch_bounds__(kWave) q_tree_kernel(LeafTreeArgs<T> a, int le
     constexpr int RB = MergeRows<T, NC>::RB, NS = Slots<NC>::NS;
     using C = Chunk<T, RB, NS>;
     __shared__ T Vl[NT];
-    __shared__ T top[NC * kTopStride];
+    __shared__ T top[4 * Slots<NC>::NS * kTopStride];
     __shared__ __align__(16) T work[PanelLds<T, RB>::kElems];
     const int lane = threadIdx.x;
     const int q = C::q(lane), p = C::p(lane);
@@ -152,23 +207,18 @@ __global__ void __launch_bounds__(kWave) q_tree_kernel(LeafTreeArgs<T> a, int le
     T* qL = a.qs.qblk + (int64_t)left * NC * NC;
     T* qR = a.qs.qblk + (int64_t)right * NC * NC;
     const T tau = lane < NC ? a.qs.tau_node[(int64_t)id * NC + lane] : T(0);
-    for (int i = lane; i < NT; i += kWave) Vl[i] = a.qs.Vn[(int64_t)id * NT + i];
-    for (int j = 0; j < NC; ++j) top[j * kTopStride + lane] = lane < NC ? qL[j * NC + lane] : T(0);
+    triangle_to_lds<T, NC>(a.qs.Vn + (int64_t)id * NT, Vl);
+    load_top<T, NC, NC, NC>(qL, top);
+    zero_spare_rows<T, NC>(top);
     wave_sync();
     C c;
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
         for (int s = 0; s < NS; ++s) c.put(r, s, T(0));
-    static_for<0, NS>([&](auto pc) {
-        constexpr int P = NS - 1 - decltype(pc)::value;
-        Chunk<T, RB, 1> x;
-        node_reflectors<T, NC, P>(x, Vl, q, p);
-        apply_panel<T, NC, RB, P / 4 + 1, P, NS, false, P == NS - 1>(x, c, top, work, tau);
-    });
+    apply_node<T, NC, NS, false>(c, Vl, top, work, tau, q, p);
     wave_sync();
-    for (int j = 0; j < NC; ++j)
-        if (lane < NC) qL[j * NC + lane] = top[j * kTopStride + lane];
+    store_top<T, NC, NC, NC>(top, qL);
 #pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
@@ -187,7 +237,7 @@ __global__ void __launch_bounds__(kWave) q_leaf_kernel(LeafTreeArgs<T> a, T* Q, 
     constexpr int CH = 16 * RPL;
     constexpr int NS = Slots<NC>::NS;
     using C = Chunk<T, RPL, NS>;
-    __shared__ T top[NC * kTopStride];
+    __shared__ T top[4 * Slots<NC>::NS * kTopStride];
     __shared__ __align__(16) T work[PanelLds<T, RPL>::kElems];
     const int lane = threadIdx.x;
     const int q = C::q(lane), p = C::p(lane);
@@ -196,7 +246,8 @@ __global__ void __launch_bounds__(kWave) q_leaf_kernel(LeafTreeArgs<T> a, T* Q, 
     const int64_t r0 = (int64_t)leaf * a.leaf_rows;
     const int64_t r1 = (r0 + a.leaf_rows < a.m) ? r0 + a.leaf_rows : a.m;
     const T* qin = a.qs.qblk + (int64_t)leaf * NC * NC;
-    for (int j = 0; j < NC; ++j) top[j * kTopStride + lane] = lane < NC ? qin[j * NC + lane] : T(0);
+    load_top<T, NC, NC, NC>(qin, top);
+    zero_spare_rows<T, NC>(top);
     wave_sync();
     if (r1 <= r0) return;
     const int64_t nchunks = (r1 - r0 + CH - 1) / CH;
@@ -217,17 +268,13 @@ __global__ void __launch_bounds__(kWave) q_leaf_kernel(LeafTreeArgs<T> a, T* Q, 
         for (int r = 0; r < RPL; ++r)
 #pragma unroll
             for (int s = 0; s < NS; ++s) c.put(r, s, T(0));
-        static_for<0, NS>([&](auto pc) {
-            constexpr int P = NS - 1 - decltype(pc)::value;
-            if (P <= plast) {
-                x = nx;
-                if constexpr (P > 0)
-                    load_reflectors<T, RPL>(nx, a.qs.V, a.qs.ldv, cbase, P - 1, n, q, p);
-                else
-                    load_reflectors<T, RPL>(nx, a.qs.V, a.qs.ldv, r0 + tn * CH, plast, n, q, p);
-                apply_panel<T, NC, RPL, RPL, P, NS, false, false>(x, c, top, work, tau);
-            }
-        });
+#pragma nounroll
+        for (int P = plast; P >= 0; --P) {
+            x = nx;
+            const bool last = P == 0;
+            load_reflectors<T, RPL>(nx, a.qs.V, a.qs.ldv, last ? r0 + tn * CH : cbase, last ? plast : P - 1, n, q, p);
+            apply_panel<T, RPL, RPL, NS, false>(4 * P, x, c, top, work, tau);
+        }
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
             const int64_t row = cbase + p + 16 * r;
@@ -263,7 +310,7 @@ __global__ void __launch_bounds__(kWave) qt_leaf_kernel(QtArgs<T> x)
     constexpr int CH = 16 * RPL;
     constexpr int NS = Slots<NC>::NS;
     using C = Chunk<T, RPL, KS>;
-    __shared__ T top[NC * kTopStride];
+    __shared__ T top[4 * Slots<NC>::NS * kTopStride];
     __shared__ __align__(16) T work[PanelLds<T, RPL>::kElems];
     const LeafTreeArgs<T>& a = x.a;
     const int lane = threadIdx.x;
@@ -273,6 +320,7 @@ __global__ void __launch_bounds__(kWave) qt_leaf_kernel(QtArgs<T> x)
     const int64_t r0 = (int64_t)leaf * a.leaf_rows;
     const int64_t r1 = (r0 + a.leaf_rows < a.m) ? r0 + a.leaf_rows : a.m;
     for (int j = 0; j < NC; ++j) top[j * kTopStride + lane] = T(0);
+    zero_spare_rows<T, NC>(top);
     wave_sync();
     const int64_t nchunks = r1 > r0 ? (r1 - r0 + CH - 1) / CH : 0;
     const int plast = (n - 1) / 4;
@@ -311,20 +359,17 @@ __global__ void __launch_bounds__(kWave) qt_leaf_kernel(QtArgs<T> x)
         } else {
             load_b(c, t);
         }
-        static_for<0, NS>([&](auto pc) {
-            constexpr int P = decltype(pc)::value;
-            if (P <= plast) {
-                v = nv;
-                const bool last = P == plast;
-                load_reflectors<T, RPL>(nv, a.qs.V, a.qs.ldv, last ? r0 + tn * CH : cbase, last ? 0 : P + 1, n, q, p);
-                apply_panel<T, NC, RPL, RPL, P, KS, true, false>(v, c, top, work, tau);
-            }
-        });
+#pragma nounroll
+        for (int P = 0; P <= plast; ++P) {
+            v = nv;
+            const bool last = P == plast;
+            load_reflectors<T, RPL>(nv, a.qs.V, a.qs.ldv, last ? r0 + tn * CH : cbase, last ? 0 : P + 1, n, q, p);
+            apply_panel<T, RPL, RPL, KS, true>(4 * P, v, c, top, work, tau);
+        }
     }
     wave_sync();
     T* out = x.tq + (int64_t)leaf * NC * kQtCols;
-    for (int j = 0; j < NC; ++j)
-        if (lane < 4 * KS) out[j * kQtCols + lane] = top[j * kTopStride + lane];
+    store_top<T, NC, 4 * KS, kQtCols>(top, out);
 }
 
 // Level `level` of the tree, leaves first: workgroup g takes the merge whose
@@ -337,7 +382,7 @@ __global__ void __launch_bounds__(kWave) qt_tree_kernel(QtArgs<T> x, int level)
     using C = Chunk<T, RB, KS>;
     const LeafTreeArgs<T>& a = x.a;
     __shared__ T Vl[NT];
-    __shared__ T top[NC * kTopStride];
+    __shared__ T top[4 * Slots<NC>::NS * kTopStride];
     __shared__ __align__(16) T work[PanelLds<T, RB>::kElems];
     const int lane = threadIdx.x;
     const int q = C::q(lane), p = C::p(lane);
@@ -348,8 +393,9 @@ __global__ void __launch_bounds__(kWave) qt_tree_kernel(QtArgs<T> x, int level)
     T* tl = x.tq + (int64_t)left * NC * kQtCols;
     const T* tr = x.tq + (int64_t)right * NC * kQtCols;
     const T tau = lane < NC ? a.qs.tau_node[(int64_t)id * NC + lane] : T(0);
-    for (int i = lane; i < NT; i += kWave) Vl[i] = a.qs.Vn[(int64_t)id * NT + i];
-    for (int j = 0; j < NC; ++j) top[j * kTopStride + lane] = lane < 4 * KS ? tl[j * kQtCols + lane] : T(0);
+    triangle_to_lds<T, NC>(a.qs.Vn + (int64_t)id * NT, Vl);
+    load_top<T, NC, 4 * KS, kQtCols>(tl, top);
+    zero_spare_rows<T, NC>(top);
     C c;
 #pragma unroll
     for (int r = 0; r < RB; ++r)
@@ -359,15 +405,9 @@ __global__ void __launch_bounds__(kWave) qt_tree_kernel(QtArgs<T> x, int level)
             c.put(r, s, row < NC ? tr[row * kQtCols + 4 * s + q] : T(0));
         }
     wave_sync();
-    static_for<0, NS>([&](auto pc) {
-        constexpr int P = decltype(pc)::value;
-        Chunk<T, RB, 1> v;
-        node_reflectors<T, NC, P>(v, Vl, q, p);
-        apply_panel<T, NC, RB, P / 4 + 1, P, KS, true, false>(v, c, top, work, tau);
-    });
+    apply_node<T, NC, KS, true>(c, Vl, top, work, tau, q, p);
     wave_sync();
-    for (int j = 0; j < NC; ++j)
-        if (lane < 4 * KS) tl[j * kQtCols + lane] = top[j * kTopStride + lane];
+    store_top<T, NC, 4 * KS, kQtCols>(top, tl);
 }
 
 // C(i, j) = D(i) T_root(i, j) for the k0-th panel of columns, D from the root's
