@@ -18,10 +18,10 @@
 // Two kernels:
 //   mixed_gram_kernel   one workgroup of two wavefronts per (row block,
 //                       instance), on the FP64 matrix cores: the operand table
-//                       of the blocked substitution (below) from R~ into LDS,
-//                       then Y = A R~^-1 and the rows' contribution to
-//                       G = Y^T Y, 32 rows at a time; the partial G goes to a
-//                       workspace slot.
+//                       of the blocked substitution (below) from R~, then
+//                       Y = A R~^-1 and the rows' contribution to G = Y^T Y,
+//                       16 rows of each wavefront at a time; the partial G goes
+//                       to a workspace slot.
 //   mixed_finish_kernel one wavefront per instance: sums the slots in a fixed
 //                       order (bit-reproducible), Cholesky with one column per
 //                       lane, a bound on kappa(A R~^-1), R = R_c R~,
@@ -50,10 +50,16 @@
 // index), and
 //     G_IJ += (Y_I)^T Y_J      for I <= J,
 // one instruction per block pair, accumulated in registers over the row block.
-// Each of the two wavefronts substitutes its own 16-row tile and then adds,
-// for both tiles, the products of half of the block pairs, so the registers of
-// a wavefront hold half of G and two wavefronts fit a SIMD: one's dependent
-// substitution chain runs beside the other's independent Gram products.
+// A wavefront takes whole tiles: it keeps all of G and most of the operands in
+// its 512 registers (one wavefront per SIMD at n > 32) and adds the products of
+// the tile before between the steps of a tile's substitution, which fills the
+// two-instruction chain.  Bound by instruction issue: at n = 50 a tile is 182
+// matrix instructions of 16 cycles and about 200 others of 5, of which the
+// operand reads from LDS were 91.  256 x 65536 x 50 takes 1.85 ms (the whole
+// call with a 4096-row sample 2370 us); with half of G per wavefront, every
+// operand read from LDS and two wavefronts per SIMD it was 2.0 ms (2510 us).
+// The loads must not be consumed before their tile: with the select of rows
+// past the end at the load, each tile waited for the next one's (2840 us).
 #pragma once
 
 #include "tsqr_device.h"
@@ -104,28 +110,51 @@ __device__ inline double substitution_operand(const float* Rt, int n, int p, int
 
 constexpr int kGramWaves = 2;
 
-// The work of one wavefront of the Gram kernel: the substitution of its own
-// tile in every iteration and, for both tiles of the iteration, the products
-// of block pairs [P0, P1).
-template <int NC, int P0, int P1>
-__device__ __forceinline__ void gram_wave(const MixedArgs& a, const double* opl,
-                                          double (&ys)[2][kGramWaves][MfmaGram<NC>::NB][kWave], int wave)
+// Operands of the substitution that a wavefront of the Gram kernel keeps in
+// registers; it reads the others from the LDS table in every tile.  Of its 512
+// registers, two go to each entry of G and to each such operand, 6 NB to the
+// tiles in flight; with less than about 112 left for the rest, the compiler
+// moves operands between the two halves of the register file instead.
+template <int NC>
+constexpr int kGramHeld = MfmaGram<NC>::NP < 200 - 3 * MfmaGram<NC>::NB - MfmaGram<NC>::NP
+                              ? MfmaGram<NC>::NP
+                              : 200 - 3 * MfmaGram<NC>::NB - MfmaGram<NC>::NP;
+
+template <int NC>
+__global__ void __launch_bounds__(kGramWaves * kWave, MfmaGram<NC>::NP <= 36 ? 2 : 1) mixed_gram_kernel(MixedArgs a)
 {
     constexpr int NB = MfmaGram<NC>::NB;
+    constexpr int NP = MfmaGram<NC>::NP;
     constexpr int W = MfmaGram<NC>::W;
-    constexpr int NQ = P1 - P0;
+    constexpr int HELD = kGramHeld<NC>;
+    // the operand table, entry (i, k) of pair p at 16 p + 4 i + k
+    __shared__ double opl[NP * 16];
+    // each wavefront's Y^T blocks, stored at the contraction position (lane
+    // (d2, d1, d0) writes where lane (d0, d1, d2) reads)
+    __shared__ double ys[kGramWaves][NB][kWave];
     const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d0 = lane & 3, d1 = (lane >> 2) & 3, d2 = lane >> 4;
     const int b = blockIdx.y;
     const int n = a.n;
-    // (the LDS offset passes through an opaque copy every iteration, so the
-    // compiler reads each operand where it is used instead of hoisting all of
-    // them into registers)
-    int lofs = 4 * d0 + d2;
-    auto opnd = [&](int p) -> double { return opl[p * 16 + lofs]; };
-    double g[NQ];
+    const float* Rt = a.Rt + (int64_t)b * n * n;
+    for (int idx = threadIdx.x; idx < NP * 16; idx += kGramWaves * kWave)
+        opl[idx] = substitution_operand(Rt, n, idx >> 4, (idx >> 2) & 3, idx & 3);
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) g[q] = 0.0;
+    for (int I = 0; I < NB; ++I) ys[wave][I][lane] = 0.0;
+    __syncthreads();
+    int lofs = 4 * d0 + d2;
+    double op[HELD];
+#pragma unroll
+    for (int p = 0; p < HELD; ++p) op[p] = opl[p * 16 + lofs];
+    auto opnd = [&](auto pc) -> double {
+        constexpr int p = decltype(pc)::value;
+        if constexpr (p < HELD) return op[p];
+        else return opl[p * 16 + lofs];
+    };
+    double g[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) g[q] = 0.0;
 
     const float* A = a.A + (int64_t)b * a.stride_a;
     const int64_t r0 = (int64_t)blockIdx.x * a.rows_per_block;
@@ -137,107 +166,97 @@ __device__ __forceinline__ void gram_wave(const MixedArgs& a, const double* opl,
     // off-diagonal blocks are zero in padding rows, and the finish kernel never
     // reads those entries.  Block J is read from the uniform column 4 jc(J),
     // jc(J) = min(J, jl) with jl = (n - 1)/4, at the per-lane offset of
-    // (column - 4 jc(J)) in [0, 3]: d2 for J < jl, eb from jl on.  Rows past
-    // the row block read as zero.
+    // (column - 4 jc(J)) in [0, 3]: d2 for J < jl, eb from jl on.  The lanes of
+    // rows past the row block read the tile's first row and count it as zero
+    // when the tile is used: a select at the load would wait for it there.
     const int trow = 4 * d1 + d0;
     const int tdst = 16 * d0 + 4 * d1 + d2;     // the d2 <-> d0 partner
     const int jl = (n - 1) >> 2;
     const int eb = ((4 * jl + d2 < n) ? 4 * jl + d2 : n - 1) - 4 * jl;
-    const int64_t offa = trow + (int64_t)d2 * a.lda;
-    const int64_t offb = trow + (int64_t)eb * a.lda;
+    const int64_t cola = (int64_t)d2 * a.lda, colb = (int64_t)eb * a.lda;
     auto load_tile = [&](float (&dst)[NB], int64_t base) {
-        const bool ok = base + trow < r1;
+        const int64_t row = base + trow < r1 ? trow : 0;
+        const int64_t offa = row + cola, offb = row + colb;
 #pragma unroll
         for (int J = 0; J < NB; ++J) {
             const int jc = J < jl ? J : jl;
             const float* __restrict__ colp = A + base + (int64_t)(4 * jc) * a.lda;
-            const float v = colp[J < jl ? offa : offb];
-            dst[J] = ok ? v : 0.0f;
+            dst[J] = colp[J < jl ? offa : offb];
         }
     };
-    // An iteration takes kGramWaves * 16 rows: wave w substitutes the tile at
-    // base + 16 w (rows past r1 are zero and add nothing), every tile's Y^T goes
-    // to LDS, and each wave adds every tile's products for its block pairs.
+    // Tile t of the wavefront is at r0 + 16 (wave + kGramWaves t).  An
+    // iteration substitutes one tile and, between the steps of that dependent
+    // chain, adds the products of the tile before (zero in the first one).
     // Tiles are loaded two iterations ahead (two register buffers, the loop
-    // unrolled by two), which keeps enough loads in flight to cover the memory
-    // latency.
+    // unrolled by two; past the last tile, that tile again with all its rows
+    // counted as zero, so that no branch stands between a load and its use).
     constexpr int64_t STEP = kGramWaves * 16;
-    int buf = 0;
+    const int64_t first = r0 + 16 * wave;
+    const int64_t last = first + (r1 - first - 1) / STEP * STEP;       // with a tile at all: first < r1
     auto iteration = [&](float (&cur)[NB], int64_t base) {
-        asm volatile("" : "+v"(lofs));
-        double z[NB];
+        if constexpr (HELD < NP) asm volatile("" : "+v"(lofs));     // operands past HELD are read where they are used
+        double z[NB], t[NB];
 #pragma unroll
-        for (int J = 0; J < NB; ++J) z[J] = (double)cur[J];
-        if (base + 2 * STEP < r1) load_tile(cur, base + 2 * STEP + 16 * wave);
+        for (int I = 0; I < NB; ++I) t[I] = ys[wave][I][lane];
+#pragma unroll
+        for (int J = 0; J < NB; ++J) z[J] = (double)(base + trow < r1 ? cur[J] : 0.0f);
+        load_tile(cur, base + 2 * STEP < last ? base + 2 * STEP : last);
+        __builtin_amdgcn_sched_barrier(0);      // the loads stay at the start of the iteration
         static_for<0, NB>([&](auto ic) {
             constexpr int I = decltype(ic)::value;
-            z[I] = mfma4(opnd(pair_index(I, I)), z[I], 0.0);          // Y_I^T
+            z[I] = mfma4(opnd(std::integral_constant<int, pair_index(I, I)>{}), z[I], 0.0);          // Y_I^T
+            static_for<NP * I / NB, NP * (I + 1) / NB>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                g[q] = mfma4(t[pair_row(q)], t[pair_col(q)], g[q]);
+            });
             static_for<I + 1, NB>([&](auto jc) {
                 constexpr int J = decltype(jc)::value;
-                z[J] = mfma4(opnd(pair_index(I, J)), z[I], z[J]);     // Z_J^T -= (R~_IJ)^T Y_I^T
+                z[J] = mfma4(opnd(std::integral_constant<int, pair_index(I, J)>{}), z[I], z[J]);     // Z_J^T -= (R~_IJ)^T Y_I^T
             });
         });
 #pragma unroll
-        for (int I = 0; I < NB; ++I) ys[buf][wave][I][tdst] = z[I];
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < kGramWaves; ++w) {
-            double t[NB];
-#pragma unroll
-            for (int I = 0; I < NB; ++I) t[I] = ys[buf][w][I][lane];
-            static_for<0, NQ>([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                g[q] = mfma4(t[pair_row(P0 + q)], t[pair_col(P0 + q)], g[q]);
-            });
-        }
-        buf ^= 1;
+        for (int I = 0; I < NB; ++I) ys[wave][I][tdst] = z[I];
+        wave_sync();
+        __builtin_amdgcn_sched_barrier(0);
     };
     float nx0[NB], nx1[NB];
-    if (r0 < r1) load_tile(nx0, r0 + 16 * wave);
-    if (r0 + STEP < r1) load_tile(nx1, r0 + STEP + 16 * wave);
-    for (int64_t base = r0; base < r1; base += 2 * STEP) {
-        iteration(nx0, base);
-        if (base + STEP < r1) iteration(nx1, base + STEP);
+    if (first < r1) {
+        load_tile(nx0, first);
+        load_tile(nx1, first + STEP < last ? first + STEP : last);
     }
+    for (int64_t base = first; base < r1; base += 2 * STEP) {
+        iteration(nx0, base);
+        iteration(nx1, base + STEP);
+    }
+    double t[NB];
+#pragma unroll
+    for (int I = 0; I < NB; ++I) t[I] = ys[wave][I][lane];
+    static_for<0, NP>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        g[q] = mfma4(t[pair_row(q)], t[pair_col(q)], g[q]);
+    });
     // the four row groups (instruction blocks, d1) hold partial sums of every
-    // block of G: add them within each 16-lane row, then the lanes with d1 = 0
-    // write block (I, J) of the upper block triangle, entry (d2, d0)
-    double* out = a.part + ((int64_t)b * a.blocks + blockIdx.x) * (W * W);
-    static_for<0, NQ>([&](auto qc) {
+    // block of G: add them within each 16-lane row, then over the wavefronts
+    // (through the operand table's LDS), and the lanes of the first wavefront
+    // with d1 = 0 write block (I, J) of the upper block triangle, entry (d2, d0)
+    __syncthreads();
+    static_for<0, NP>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         double v = g[q];
         v = v + dpp_mov<0x124>(v);    // row_ror:4
         v = v + dpp_mov<0x128>(v);    // row_ror:8
-        if (d1 == 0) out[(4 * pair_row(P0 + q) + d2) * W + 4 * pair_col(P0 + q) + d0] = v;
+        g[q] = v;
+        if (wave == 1 && d1 == 0) opl[q * 16 + 4 * d2 + d0] = v;
     });
-}
-
-template <int NC>
-__global__ void __launch_bounds__(kGramWaves * kWave) mixed_gram_kernel(MixedArgs a)
-{
-    constexpr int NB = MfmaGram<NC>::NB;
-    constexpr int NP = MfmaGram<NC>::NP;
-    constexpr int Q = (NP + kGramWaves - 1) / kGramWaves;
-    // the operand table, entry (i, k) of pair p at 16 p + 4 i + k
-    __shared__ double opl[NP * 16];
-    // Y^T blocks of the two tiles of an iteration (one per wave), stored at the
-    // contraction position (lane (d2, d1, d0) writes where lane (d0, d1, d2)
-    // reads), double-buffered across iterations
-    __shared__ double ys[2][kGramWaves][NB][kWave];
-    const int b = blockIdx.y;
-    const float* Rt = a.Rt + (int64_t)b * a.n * a.n;
-    for (int idx = threadIdx.x; idx < NP * 16; idx += kGramWaves * kWave)
-        opl[idx] = substitution_operand(Rt, a.n, idx >> 4, (idx >> 2) & 3, idx & 3);
     __syncthreads();
-    // wave w owns block pairs [w Q, (w + 1) Q)
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    static_for<0, kGramWaves>([&](auto wc) {
-        constexpr int w = decltype(wc)::value;
-        constexpr int P0 = w * Q < NP ? w * Q : NP;
-        constexpr int P1 = (w + 1) * Q < NP ? (w + 1) * Q : NP;
-        if (wave == w) gram_wave<NC, P0, P1>(a, opl, ys, w);
+    if (wave != 0 || d1 != 0) return;
+    double* out = a.part + ((int64_t)b * a.blocks + blockIdx.x) * (W * W);
+    static_for<0, NP>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        out[(4 * pair_row(q) + d2) * W + 4 * pair_col(q) + d0] = g[q] + opl[q * 16 + 4 * d2 + d0];
     });
 }
+static_assert(kGramWaves == 2, "the sum over wavefronts is written for two");
 
 // bound on ||Rc||_F ||Rc^-1||_F (>= kappa_2(A R~^-1)) for a trusted correction;
 // an FP32 R~ of a matrix with kappa(A) <= 1e8 gives about n (1 + kappa(A) 2^-24)
