@@ -118,7 +118,13 @@ struct MergeRows {
     static constexpr int RB = sizeof(T) == 8 ? (4 * Slots<NC>::NS + 15) / 16 : 4;
 };
 
-constexpr int kMaxGrowth = 16;
+// The limit trades passes against accuracy where columns are nearly dependent.
+// 200001 x 37 with singular values over six decades, FP64, three inputs, the
+// largest error of R against an 80-bit reference: limit 16: 232-270 us,
+// 1.1e-15; 8: 302-319 us, 3.3e-16; 4: 346-381 us, 3.1e-16; one column at a time
+// on the vector units: 316 us, 4.6e-16.  Columns of moderate condition never
+// reach any of these.
+constexpr int kMaxGrowth = 10;
 
 // old with the banks (quads of a 16-lane row) in BANKS replaced by x moved by CTRL
 template <int CTRL, int BANKS>
@@ -145,13 +151,46 @@ __device__ __forceinline__ double quad_sums(double a, double b, double c, double
     // even quads add their right neighbour in ac, odd quads their left one in bd
     return dpp_into<0xE4, 0xA>(ac, bd) + dpp_into<0x124, 0xA>(dpp_mov<0x12C>(ac), bd);
 }
-// (in FP32 an addition takes its operand through DPP, so adding first and
-// merging afterwards is shorter)
-__device__ __forceinline__ float quad_sums(float a, float b, float c, float d)
+// In FP32 an addition takes its operand through DPP, so adding first and
+// merging afterwards is shorter.  All four rows of the accumulators step by
+// step: a DPP operand may be read only three instructions after it is written,
+// and the other rows fill that gap (one row after the other, a panel's sums
+// held 38 wait instructions; 4117 x 28: 69.0 us, now 64.8).  Chunks of more
+// than 8 rows per lane run two wavefronts to a SIMD, which hides the waits, and
+// have no registers for it: they go row by row (Rows; 2^22 x 50 with 12 rows
+// per lane: 638 us step by step, 625 row by row).
+template <bool Rows>
+__device__ __forceinline__ float4v quad_sums(float4v a, float4v b, float4v c, float4v d)
 {
-    const float ac = dpp_into<0xE4, 0xC>(a + dpp_mov<0x128>(a), c + dpp_mov<0x128>(c));
-    const float bd = dpp_into<0xE4, 0xC>(b + dpp_mov<0x128>(b), d + dpp_mov<0x128>(d));
-    return dpp_into<0xE4, 0xA>(ac + dpp_mov<0x12C>(ac), bd + dpp_mov<0x124>(bd));
+    float4v ac, bd, x;
+    if constexpr (Rows) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float e = dpp_into<0xE4, 0xC>(a[i] + dpp_mov<0x128>((float)a[i]), c[i] + dpp_mov<0x128>((float)c[i]));
+            const float o = dpp_into<0xE4, 0xC>(b[i] + dpp_mov<0x128>((float)b[i]), d[i] + dpp_mov<0x128>((float)d[i]));
+            ac[i] = dpp_into<0xE4, 0xA>(e + dpp_mov<0x12C>(e), o + dpp_mov<0x124>(o));
+        }
+        return ac;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ac[i] = a[i] + dpp_mov<0x128>((float)a[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = c[i] + dpp_mov<0x128>((float)c[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ac[i] = dpp_into<0xE4, 0xC>((float)ac[i], (float)x[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bd[i] = b[i] + dpp_mov<0x128>((float)b[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = d[i] + dpp_mov<0x128>((float)d[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bd[i] = dpp_into<0xE4, 0xC>((float)bd[i], (float)x[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ac[i] = ac[i] + dpp_mov<0x12C>((float)ac[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bd[i] = bd[i] + dpp_mov<0x124>((float)bd[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ac[i] = dpp_into<0xE4, 0xA>((float)ac[i], (float)bd[i]);
+    return ac;
 }
 
 // The sum over the four quads of each 16-lane row, in all four.
@@ -260,24 +299,41 @@ __device__ __forceinline__ void panel_products(const Chunk<float, RB, NX>& x, co
         });
     // add the sixteen blocks: within the 16-lane rows, then over the rows, slot s
     // ending in quad s
+    float4v t4[4];
+    static_for<T0, T1>([&](auto tc) {
+        constexpr int t = decltype(tc)::value, a = 4 * t;
+        if constexpr (Gr::live(a) == Gr::live(a + 3)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t4[t][i] = quad_sum((float)G[Gr::live(a)][i]);
+        } else {
+            t4[t] = quad_sums<(RB > 8)>(G[Gr::live(a)], G[Gr::live(a + 1)], G[Gr::live(a + 2)], G[Gr::live(a + 3)]);
+        }
+    });
+    static_for<0, T0>([&](auto tc) { t4[decltype(tc)::value] = t4[T0]; });
+    static_for<T1, 4>([&](auto tc) { t4[decltype(tc)::value] = t4[T1 - 1]; });
+    float u[4], v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float t4[4];
-        static_for<T0, T1>([&](auto tc) {
-            constexpr int t = decltype(tc)::value, a = 4 * t;
-            if constexpr (Gr::live(a) == Gr::live(a + 3))
-                t4[t] = quad_sum((float)G[Gr::live(a)][i]);
-            else
-                t4[t] = quad_sums((float)G[Gr::live(a)][i], (float)G[Gr::live(a + 1)][i],
-                                  (float)G[Gr::live(a + 2)][i], (float)G[Gr::live(a + 3)][i]);
-        });
-        static_for<0, T0>([&](auto tc) { t4[decltype(tc)::value] = t4[T0]; });
-        static_for<T1, 4>([&](auto tc) { t4[decltype(tc)::value] = t4[T1 - 1]; });
-        swap_rows16(t4[0], t4[1]);
-        swap_rows16(t4[2], t4[3]);
-        float u = t4[0] + t4[1], v = t4[2] + t4[3];
-        swap_rows32(u, v);
-        g[i] = u + v;
+        float x = t4[0][i], y = t4[1][i];
+        swap_rows16(x, y);
+        u[i] = x + y;
+    }
+    if constexpr (T1 <= 2) {
+        // no columns in the upper half of the lanes
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = u[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x = t4[2][i], y = t4[3][i];
+            swap_rows16(x, y);
+            v[i] = x + y;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        swap_rows32(u[i], v[i]);
+        g[i] = u[i] + v[i];
     }
 }
 
