@@ -147,8 +147,8 @@ int64_t tsqr_workspace_bytes(tsqr_handle_t handle, int64_t m, int64_t n, int dty
  *        256-byte aligned; contents on entry are irrelevant and are
  *        overwritten; calls that may run concurrently must not share a
  *        workspace.
- * The call makes two kernel launches (a small one that zeroes the tree
- * counters, then the factorisation) and allocates nothing.
+ * The call makes one kernel launch, with more than four leaves a small one in
+ * front of it that zeroes the tree counters, and allocates nothing.
  * m = 0 gives R = 0; m < n gives zero rows m..n-1 (the missing rows are
  * read as zeros).  Argument codes: -1 handle, -2 m, -3 n, -4 A, -5 lda, -6 R,
  * -7 ldr, -8 ws, -9 ws_bytes. */

@@ -1,42 +1,35 @@
 // tsqr_device.h -- gfx950 device code for the R factor of a tall-skinny matrix
 // by Householder TSQR (Langou, arXiv:1002.4250, sections 2-3).
 //
-// Execution model (one wavefront of 64 lanes per workgroup):
+// Execution model (wavefronts of 64 lanes, four to a workgroup where there is
+// more than one leaf):
 //   * A leaf is a contiguous block of rows of A.  Its wavefront keeps the n-by-n
 //     triangle R in LDS (packed by rows) and streams the block through
 //     registers in chunks of 16*RPL rows.  Each chunk C is merged into R by
-//     R := R-factor of [R; C]: for every column j one Householder reflector
-//     built from R(j,j) and C(:,j) is applied to the trailing columns (the
-//     structured update of Table 3 with R2 replaced by a dense chunk: a flat
-//     tree inside the leaf; section 2 allows any tree).
+//     R := R-factor of [R; C] (the structured update of Table 3 with R2
+//     replaced by a dense chunk: a flat tree inside the leaf; section 2 allows
+//     any tree), four columns at a time on the matrix cores (tsqr_panel.h, with
+//     the register layout and the arithmetic).
 //   * Leaves then combine with the paper's operator qr(R1, R2) over a binary
-//     tree pairing leaf i with i + 2^level (lower index on top), the merge done
-//     by whichever wavefront of the pair arrives last (atomic ticket), so no
-//     wavefront ever waits on another.  A merge has only NC rows, so it uses a
-//     second layout: one column of R2 per lane (merge_columns).  Workgroups
-//     are numbered onto leaves so that tree siblings share an XCD and its L2
-//     (xcd_local_leaf).
+//     tree pairing leaf i with i + 2^level (lower index on top): within a
+//     workgroup through LDS, above that by whichever wavefront of the pair
+//     arrives last (atomic ticket), so no wavefront ever waits on another.  A
+//     merge is the same panel step on the lower triangle's rows (merge_panels).
+//     Workgroups are numbered onto leaves so that tree siblings share an XCD
+//     and its L2 (xcd_local_leaf).
 //   * The root flips rows with a negative diagonal (section 2's positive
 //     diagonal convention) and writes R.
+//   * The operator's own entry point (Table 3) takes one column of R2 per lane
+//     and one reflector at a time (merge_columns).
 //
-// Register layout of a chunk: the wavefront is four 16-lane rows q = 0..3.
-// Lane (q, p) = lane 16q + p holds chunk rows p + 16r (r < RPL) of the
-// columns k = 4s + q (slot s < NS = ceil(NC/4)): the columns are dealt
-// cyclically to the four lane rows, the matrix rows to the 16 lanes of a lane
-// row.  A dot product over the chunk's rows is then a sum over RPL registers
-// and over only 16 lanes, which goes through LDS in one transpose (each lane
-// adds 16 values); the pivot column reaches all lane rows by one ds_bpermute
-// per register, and each column's update coefficient reaches its lane row by
-// a DPP row broadcast.
-//
-// Per Householder step j (x = C(:,j), k > j the trailing columns):
-//     sigma^2 = x.x,  d_k = x.C(:,k)
-//     beta = -sign(alpha) sqrt(alpha^2 + sigma^2), alpha = R(j,j)
-//     tau = (beta - alpha)/beta, s = 1/(alpha - beta)        (v = s x)
-//     w_k = R(j,k) + s d_k,  R(j,k) -= tau w_k,  C(:,k) -= (tau s w_k) x
-// which is the reflector generation and rank-1 update of Table 3 with the
-// Householder vector kept unscaled (v = s x) so that no lane has to rescale
-// its rows before the dot products.
+// What bounds it: instruction issue of one wavefront per SIMD.  A matrix
+// instruction of one wavefront and a vector instruction of another do not
+// overlap on a SIMD, so a panel costs its matrix instructions (16 cycles in
+// FP64, 8 in FP32) plus about 5 cycles for each of some 300 others, most of
+// them the four dependent reflectors.  A chunk of 128 rows at n = 50 in FP64
+// takes 21 us on its own (about 3900 cycles a panel), a merge of two triangles
+// 16 us.  One column at a time on the vector units the chunk took 37 us, and
+// 2^22 x 50 1437 us per call in FP64 and 767 us in FP32; now 898 and 625 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -52,8 +45,6 @@ namespace tsqr {
 namespace dev {
 
 constexpr int kWave = 64;
-constexpr int kRedStride = 17;                  // odd stride: conflict-free LDS transpose
-constexpr int kRedElems = 4 * 16 * kRedStride;  // one 16 x 17 tile per lane row
 
 template <int NC>
 struct Tri {
@@ -63,13 +54,6 @@ struct Tri {
     static constexpr int kPadded = kSize + 64;
     // packed row-major upper triangle: row j starts at off(j), entry (j,k) at off(j)+k-j
     static constexpr __host__ __device__ int off(int j) { return j * NC - (j * (j - 1)) / 2; }
-};
-
-// The leaf's reduction tiles and, in the tree, the partner's triangle share
-// one LDS buffer: they are never live at the same time.
-template <int NC>
-struct LdsScratch {
-    static constexpr int kElems = kRedElems > Tri<NC>::kPadded ? kRedElems : Tri<NC>::kPadded;
 };
 
 template <int NC>
@@ -104,17 +88,6 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x)
 {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-
-// Sum over the 16 lanes of each lane row, returned in all 16 (bit-identical).
-template <typename T>
-__device__ __forceinline__ T row_allreduce16(T x)
-{
-    x = x + dpp_mov<0x128>(x);   // row_ror:8
-    x = x + dpp_mov<0x124>(x);   // row_ror:4
-    x = x + dpp_mov<0x122>(x);   // row_ror:2
-    x = x + dpp_mov<0x121>(x);   // row_ror:1
-    return x;
 }
 
 // Fused multiply-add and absolute value in the element type (the generic
@@ -329,15 +302,10 @@ struct VSink {
 // registers (ds_bpermute) and forms its own dot product with it locally
 // (lane J's is sigma^2, which all lanes then read from its register), so a
 // step has no cross-lane reduction, and lane k > J updates R1(J, k) and its
-// column.  Used by the reduction tree and the operator entry point,
-// where the operands have only NC rows and the length of the dependent chain
-// of NC steps, not the arithmetic, sets the time.
-//
-// Mode::Operator also leaves the Householder vectors in v (lane J's column
-// becomes s x, or stays x for an identity reflector) and the tau in tau_out.
-enum class Mode { Merge, Operator };
-
-template <typename T, int NC, Mode M>
+// column.  One wavefront, bound by its chain of NC dependent steps.  Leaves the
+// Householder vectors in v (lane J's column becomes s x, or stays x for an
+// identity reflector) and the tau in tau_out.
+template <typename T, int NC>
 __device__ __forceinline__ void merge_columns(T (&v)[NC], T* Rs, T* tau_out)
 {
     const int lane = lane_id();
@@ -368,12 +336,10 @@ __device__ __forceinline__ void merge_columns(T (&v)[NC], T* Rs, T* tau_out)
         const T f = own ? h.ts * w : T(0);
 #pragma unroll
         for (int i = 0; i <= J; ++i) v[i] = fmadd(-f, x[i], v[i]);
-        if constexpr (M == Mode::Operator) {
-            const bool mine = (lane == J) && (h.tau != T(0));
+        const bool mine = (lane == J) && (h.tau != T(0));
 #pragma unroll
-            for (int i = 0; i <= J; ++i) v[i] = mine ? h.s * x[i] : v[i];
-            if (lane == 0) tau_out[J] = h.tau;
-        }
+        for (int i = 0; i <= J; ++i) v[i] = mine ? h.s * x[i] : v[i];
+        if (lane == 0) tau_out[J] = h.tau;
         lds_order();
     });
 }
@@ -777,7 +743,7 @@ __global__ void __launch_bounds__(kWave) qr_uppers_kernel(int n, T* R1, T* R2, T
     T v[NC];
     triangle_column<T, NC>(R2s, v);
     wave_sync();
-    merge_columns<T, NC, Mode::Operator>(v, Rs, taus);
+    merge_columns<T, NC>(v, Rs, taus);
     wave_sync();
     for (int idx = lane; idx < n * n; idx += kWave) {
         const int i = idx % n, k = idx / n;

@@ -1,8 +1,10 @@
 // tsqr_instances.h -- the kernel instantiations compiled into libtsqr.so.
 // Each X(tag, NC, RPL) is a leaf+tree kernel for element type tag (f64/f32),
-// NC compiled columns and RPL rows per lane (a chunk is 16*RPL rows); each O(tag, NC) an operator
-// kernel (with the mixed-precision kernels for f64); each Q(tag, NC, RPL) the Q-factor kernels.  The build compiles one translation unit per entry (in parallel) and
-// the C-ABI layer dispatches through the same lists.
+// NC compiled columns and RPL rows per lane (a chunk is 16*RPL rows); each
+// O(tag, NC) an operator kernel (with the mixed-precision kernels for f64);
+// each Q(tag, NC, RPL) the Q-factor kernels.  The build compiles one translation
+// unit per entry (in parallel) and the C-ABI layer dispatches through the same
+// lists.
 #pragma once
 
 #define TSQR_LEAF_INSTANCES(X) \

@@ -121,8 +121,8 @@ struct MergeRows {
 // The limit trades passes against accuracy where columns are nearly dependent.
 // 200001 x 37 with singular values over six decades, FP64, three inputs, the
 // largest error of R against an 80-bit reference: limit 16: 232-270 us,
-// 1.1e-15; 8: 302-319 us, 3.3e-16; 4: 346-381 us, 3.1e-16; one column at a time
-// on the vector units: 316 us, 4.6e-16.  Columns of moderate condition never
+// 1.1e-15; 10: 276-311 us, 4.7e-16; 8: 302-319 us, 3.3e-16; 4: 346-381 us,
+// 3.1e-16; one column at a time on the vector units: 316 us, 4.6e-16.  Columns of moderate condition never
 // reach any of these.
 constexpr int kMaxGrowth = 10;
 

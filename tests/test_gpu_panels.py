@@ -1,0 +1,138 @@
+"""The four-column panels of the leaves, merges and Q passes, and the Gram pass
+of the mixed-precision correction, at the sizes where they can go wrong: the
+edges of the compiled column widths (8, 24, 40 among them), one to five leaves
+(one launch without counters up to four, the last group partly filled, the
+first tree level through memory), a ragged last chunk, panels that have to be
+cut, leaves cut shorter so that a batch fills the device, and row counts around
+the 16-row tiles of the Gram pass.
+
+Tolerances: the backward-error gates of ``gates`` (they hold at any condition
+number), and 900 u for Q R = A, Q^T A = R and the orthogonality of Q, the bound
+that the Q tests use in FP64 (1e-13).  Orthogonality is asked for where A has
+well-conditioned columns only: the first chunk is stacked under a zero block,
+which Q leaves out, so Q's columns for dependent columns of A have rows there
+(a zero column of A gives a zero column of Q).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from gates import GRAM32, GRAM64
+from paper_1002_4250_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1002_4250_amd import tsqr  # noqa: E402
+
+DT = {"f64": (np.float64, GRAM64, 1e-13), "f32": (np.float32, GRAM32, 900 * 2.0 ** -24)}
+
+
+def relF(X, Y):
+    return float(np.linalg.norm(X - Y) / max(np.linalg.norm(Y), 1e-300))
+
+
+def to_dev(A):
+    return torch.from_numpy(np.ascontiguousarray(A.T)).cuda().t()
+
+
+def check_r_and_q(A, leaf_rows, gram, tol, orthogonal=True):
+    """R and Q of A against the oracle's gates, and R the same bit for bit from every entry point."""
+    n = A.shape[1]
+    h = tsqr.handle(0)
+    tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, leaf_rows)
+    try:
+        Ad = to_dev(A)
+        R = tsqr.geqr_r(Ad).cpu().numpy()
+        Q, Rq = (x.cpu().numpy() for x in tsqr.geqr_qr(Ad))
+        f = tsqr.Factorization(Ad)
+        QtA = f.apply_qt(Ad).cpu().numpy().astype(np.float64)
+        Rf = f.R.cpu().numpy()
+    finally:
+        tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, 0)
+    assert np.array_equal(R, Rq) and np.array_equal(R, Rf)
+    assert np.all(np.tril(R, -1) == 0) and not np.any(np.signbit(np.diag(R)))
+    A, Q, R = A.astype(np.float64), Q.astype(np.float64), R.astype(np.float64)
+    assert oracle.gram_residual(A, R) < gram
+    if orthogonal:
+        assert np.linalg.norm(Q.T @ Q - np.eye(n)) / np.sqrt(n) < tol
+    assert relF(Q @ R, A) < tol
+    assert relF(QtA, R) < tol
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n,leaves", [(8, 1), (8, 3), (9, 2), (24, 4), (24, 5), (25, 1), (40, 2), (40, 5), (41, 3),
+                                      (41, 4), (3, 5), (64, 3), (50, 7)])
+def test_widths_and_leaf_counts(n, leaves, dt):
+    npdt, gram, tol = DT[dt]
+    A = inputs.uniform(128 * leaves - 37, n, 700 + n, npdt)
+    check_r_and_q(A, 128, gram, tol)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n,m", [(12, 300), (50, 900)])
+@pytest.mark.parametrize("kind", ["equal", "close", "closer", "zero", "graded"])
+def test_cut_panels(n, m, kind, dt):
+    npdt, gram, tol = DT[dt]
+    rng = np.random.default_rng(n)
+    A = rng.uniform(-1, 1, (m, n))
+    eps = float(np.finfo(npdt).eps)
+    for j in range(1, n, 3):                         # within panels and across their edges
+        noise = rng.uniform(-1, 1, m)
+        if kind == "equal":
+            A[:, j] = A[:, j - 1]
+        elif kind == "close":
+            A[:, j] = A[:, j - 1] + eps ** 0.25 * noise
+        elif kind == "closer":
+            A[:, j] = 2.0 * A[:, j - 1] + eps ** 0.75 * noise
+        elif kind == "zero":
+            A[:, j] = 0.0
+        else:
+            A[:, j] *= eps ** (j / n)
+    check_r_and_q(np.asfortranarray(A.astype(npdt)), 128, gram, tol, orthogonal=False)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("sizes", [(30000,), (8192, 8193, 64, 20000, 1), (70000, 300)])
+def test_batch_leaves_fill_the_device(sizes, dt):
+    npdt, gram, _ = DT[dt]
+    n = 30
+    offsets = [int(o) for o in np.concatenate(([0], np.cumsum(sizes)[:-1])) * n]
+    A = [inputs.uniform(m, n, 900 + m, npdt) for m in sizes]
+    flat = np.concatenate([np.ascontiguousarray(a.T).reshape(-1) for a in A])
+    plan = tsqr.BatchPlan(list(sizes), offsets, n, torch.from_numpy(flat).dtype)
+    _, _, leaf_rows = plan.info()
+    assert 0 < leaf_rows < 8192                      # shorter than on a batch that fills the device by itself
+    R = plan.run(torch.from_numpy(flat).cuda()).cpu().numpy()
+    h = tsqr.handle(0)
+    tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, leaf_rows)
+    try:
+        single = [tsqr.geqr_r(to_dev(a)).cpu().numpy() for a in A]
+    finally:
+        tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, 0)
+    for b, a in enumerate(A):
+        assert np.array_equal(R[b].T, single[b]), b
+        assert oracle.gram_residual(a.astype(np.float64), R[b].T.astype(np.float64)) < gram, b
+
+
+@pytest.mark.parametrize("n,m", [(8, 1025), (9, 1039), (24, 1024), (33, 1040), (40, 1055), (50, 1056), (50, 1057),
+                                 (64, 2049), (64, 2071), (50, 40)])
+def test_mixed_gram_tiles(n, m):
+    batch = 3
+    A = [inputs.uniform(m, n, 40 + b, np.float32) for b in range(batch)]
+    if m == 40:                                      # ten rows twice: rank 40, the FP64 path may take over
+        A = [np.concatenate([a, a[:10]]) for a in A]
+    rows = A[0].shape[0]
+    flat = np.concatenate([np.ascontiguousarray(a.T).reshape(-1) for a in A])
+    plan = tsqr.MixedPlan(batch, rows, n)
+    R, fb = plan.run(torch.from_numpy(flat).cuda())
+    R = R.cpu().numpy()
+    for b, a in enumerate(A):
+        a64 = np.asfortranarray(a.astype(np.float64))
+        assert oracle.gram_residual(a64, R[b].T) < GRAM64, b
+        if m > 40:
+            assert int(fb[b]) == 0, b
+            assert relF(R[b].T, oracle.r_factor(a64)) < 1e-12, b
