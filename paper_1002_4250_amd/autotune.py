@@ -33,7 +33,13 @@ DEFAULT_TABLE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning
 DTYPES = {"f64": tsqr.TSQR_F64, "f32": tsqr.TSQR_F32}
 M_BUCKETS = [1 << 12, 1 << 14, 1 << 16, 1 << 18, 1 << 20, 1 << 22]
 WAVES_PER_CU = [1, 2, 4, 8, 16]
-BATCH_LEAF_CHUNKS = [16, 32, 64, 128, 256]
+BATCH_LEAF_CHUNKS = [16, 32, 43, 64, 128, 256]
+# No candidate longer than this (plus a chunk): with longer leaves a batch of
+# 2^24 rows does not give every resident wavefront a leaf.  256 of 65536 x 50
+# take 3.10 ms in FP64 with leaves of 16384 rows and 5.80 ms with 32768; FP32
+# 1.92 ms with 8256 and 2.62 ms with 12288, and the ragged batch tuned on here
+# tells these apart by less than 0.5%.
+BATCH_LEAF_ROWS = {"f64": 2 ** 24 // 1024, "f32": 2 ** 24 // 2048}
 M_MAX_LAST = (1 << 62)
 
 
@@ -110,6 +116,8 @@ def tune_batch(torch, h, dtype_name, n, data, reps):
         for rpl in tsqr.tsqr_rows_per_lane_compiled(code, n):
             for k in BATCH_LEAF_CHUNKS:
                 L = 16 * rpl * k
+                if L >= BATCH_LEAF_ROWS[dtype_name] + 16 * rpl:
+                    continue
                 tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_ROWS_PER_LANE, rpl)
                 tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, L)
                 plan = tsqr.BatchPlan(sizes, offsets, n, tdt, h=h)
