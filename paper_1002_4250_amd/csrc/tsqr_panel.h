@@ -464,7 +464,12 @@ __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4
 // The general form: columns below lo are done already; the panel is cut in
 // front of the first column (after lo) whose growth is over the limit, and the
 // result is that column, or NJ.  nf is zero for columns outside [lo, hi); in the
-// lanes of columns left of hi it is valid with WQ only.
+// lanes of columns left of hi it is valid with WQ only.  A sigma^2 that is not
+// a normal number calls for the identity only where it is a sum of squares as it
+// stands.  After lo it is a difference with an error of about eps grow, and
+// behind one that came out as zero or negative there may be a column of norm
+// sqrt(eps grow), whatever alpha hides in the growth test: the panel is cut
+// there too.
 template <typename T, int J0, int NJ, bool WQ>
 __device__ __forceinline__ int panel_reflectors_cut(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4],
                                                     int lane, int lo)
@@ -479,12 +484,14 @@ __device__ __forceinline__ int panel_reflectors_cut(T (&g)[4], T (&r)[4], T (&nf
         const T alpha = lane_value(r[j], J0 + j);
         const T sigma2 = lane_value(g[j], J0 + j);
         const T S = fmadd(alpha, alpha, sigma2);
+        const bool normal = __builtin_amdgcn_ballot_w64(sigma2 >= Limits<T>::tiny) != 0;
         if constexpr (j > 0) {
-            const uint64_t over = __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S));
+            const uint64_t over = __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) |
+                                  (normal ? 0 : __builtin_amdgcn_ballot_w64(grow != T(0)));
             if (((over >> (J0 + j)) & 1) && j > lo && j < hi) hi = j;
         }
         PanelScalars<T> h = panel_scalars(alpha, S);
-        if (__builtin_amdgcn_ballot_w64(sigma2 >= Limits<T>::tiny) == 0 || j < lo || j >= hi) [[unlikely]] {
+        if (!normal || j < lo || j >= hi) [[unlikely]] {
             h.z = T(-1);                  // an identity reflector
             h.sy = T(0);
             h.beta = alpha;

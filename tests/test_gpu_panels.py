@@ -96,6 +96,25 @@ def test_cut_panels(n, m, kind, dt):
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n", [4, 8, 15])
+@pytest.mark.parametrize("leaf_rows", [256, 128])    # the two blocks as chunks of a leaf, and as leaves that merge
+def test_columns_dependent_in_the_lower_block_only(n, leaf_rows, dt):
+    """Below, column 4 i + 1 is column 4 i plus e times column 4 i + 2; above, it
+    has a large part of its own, so that R's diagonal hides how little is left
+    of it below.  What is left has inner products with the later columns."""
+    npdt, gram, tol = DT[dt]
+    e = 3e-9 if dt == "f64" else 1e-4
+    for seed in range(8):
+        rng = np.random.default_rng(100 + seed)
+        A = rng.uniform(-1, 1, (256, n))
+        for j in range(0, n - 2, 4):
+            top, u = A[:128, j], A[:128, j + 1]
+            A[:128, j + 1] = top + u - top * (top @ u) / (top @ top)
+            A[128:, j + 1] = A[128:, j] + e * A[128:, j + 2]
+        check_r_and_q(np.asfortranarray(A.astype(npdt)), leaf_rows, gram, tol)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("sizes", [(30000,), (8192, 8193, 64, 20000, 1), (70000, 300)])
 def test_batch_leaves_fill_the_device(sizes, dt):
     npdt, gram, _ = DT[dt]
