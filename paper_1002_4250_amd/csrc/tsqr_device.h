@@ -71,8 +71,14 @@ __device__ __forceinline__ void static_for(F&& f)
 }
 
 template <typename T> struct Limits;
-template <> struct Limits<double> { static constexpr double tiny = 2.2250738585072014e-308; };
-template <> struct Limits<float> { static constexpr float tiny = 1.17549435e-38f; };
+template <> struct Limits<double> {
+    static constexpr double tiny = 2.2250738585072014e-308;     // the smallest normal number
+    static constexpr int tiny_high = 0x00100000;                // its high_word
+};
+template <> struct Limits<float> {
+    static constexpr float tiny = 1.17549435e-38f;
+    static constexpr int tiny_high = 0x00800000;
+};
 
 // ---- cross-lane primitives -------------------------------------------------
 
@@ -96,8 +102,11 @@ __device__ __forceinline__ double fmadd(double a, double b, double c) { return _
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double absv(double x) { return __builtin_fabs(x); }
 __device__ __forceinline__ float absv(float x) { return __builtin_fabsf(x); }
-// The hardware's maximum and minimum as they stand (a NaN gives the other
-// operand); the builtins quiet their operands first, one more instruction each.
+// The hardware's maximum as it stands (a NaN gives the other operand); the
+// builtin quiets its operands first, one more instruction each.  The operands are
+// vector registers: a scalar register that a lane read has just written must not
+// be read for two wait states, and the compiler sees to that outside inline
+// assembly only.
 __device__ __forceinline__ double max_raw(double a, double b)
 {
     double r;
@@ -110,18 +119,10 @@ __device__ __forceinline__ float max_raw(float a, float b)
     asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
-__device__ __forceinline__ double min_raw(double a, double b)
-{
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "s"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ float min_raw(float a, float b)
-{
-    float r;
-    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "s"(a), "v"(b));
-    return r;
-}
+// The word that holds sign, exponent and the leading bits: as an integer, its
+// order is that of non-negative numbers, with every negative one below them
+__device__ __forceinline__ int high_word(double x) { return __double2hiint(x); }
+__device__ __forceinline__ int high_word(float x) { return __float_as_int(x); }
 // The sign bit of x in place, and a non-negative x with that sign
 __device__ __forceinline__ unsigned sign_of(double x) { return (unsigned)__double2hiint(x) & 0x80000000u; }
 __device__ __forceinline__ unsigned sign_of(float x) { return (unsigned)__float_as_int(x) & 0x80000000u; }

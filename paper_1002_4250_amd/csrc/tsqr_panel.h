@@ -430,7 +430,8 @@ template <typename T, int J0, int NJ, bool WQ>
 __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4], int lane)
 {
     T n[4][4], alpha[4], sigma2[4];
-    T grow = T(0), least = T(0);
+    T grow = T(0);
+    int least = 0;                        // the least sigma^2 (by its high word: integers stay on the scalar unit)
     uint64_t over = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) nf[j] = tau[j] = s[j] = T(0);
@@ -439,7 +440,7 @@ __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4
         alpha[j] = lane_value(r[j], J0 + j);
         sigma2[j] = lane_value(g[j], J0 + j);
         const T S = fmadd(alpha[j], alpha[j], sigma2[j]);
-        least = j == 0 ? sigma2[j] : min_raw(sigma2[j], least);
+        least = j == 0 || high_word(sigma2[j]) < least ? high_word(sigma2[j]) : least;
         if constexpr (j > 0)
             over |= __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) & ((uint64_t)1 << (J0 + j));
         const PanelScalars<T> h = panel_scalars(alpha[j], S);
@@ -449,7 +450,7 @@ __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4
     });
     panel_coefficients<T, NJ>(nf, n);
     bool good = over == 0;
-    if (__builtin_amdgcn_ballot_w64(least < Limits<T>::tiny) != 0) [[unlikely]] {
+    if (least < Limits<T>::tiny_high) [[unlikely]] {
         if constexpr (WQ) good = false;   // a stored reflector has to be the identity
 #pragma unroll
         for (int j = 0; j < NJ; ++j)

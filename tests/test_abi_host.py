@@ -711,3 +711,16 @@ def test_geqr_r_stamped_argument_checks(ph):
     assert f(ph, m, n, 1, m, 1, n, 256, need - 1, 1, None) == -9
     assert f(ph, m, n, 1, m, 1, n, 256, need, None, None) == -10
     assert f(ph, m, n, 1, m, 1, n, 256, need, 1, None) == tsqr.TSQR_ERR_NO_DEVICE
+
+
+def test_inline_assembly_reads_no_scalar_register():
+    """An instruction in inline assembly must not take a scalar register as an
+    operand: one that a lane read has just written may not be read by a vector
+    instruction for two wait states, which the compiler only sees to outside
+    inline assembly.  (Empty statements, which only make a value opaque, may.)"""
+    csrc = os.path.join(ROOT, "paper_1002_4250_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for stmt in re.findall(r"\basm\b[^;]*;", text):
+            if not re.search(r'\(\s*""', stmt):
+                assert '"s"' not in stmt and '"+s"' not in stmt, (name, stmt)

@@ -115,6 +115,19 @@ def test_columns_dependent_in_the_lower_block_only(n, leaf_rows, dt):
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n", [8, 23, 50])
+def test_zero_column_under_a_diagonal(n, dt):
+    """Columns that are zero from the second chunk on keep their rows of R up to
+    a reflection, the same in every entry point."""
+    npdt, gram, tol = DT[dt]
+    A = inputs.uniform(700, n, 60 + n, npdt)
+    for j in (0, 2, 5, n - 1):
+        A[128:, j] = 0
+    for leaf_rows in (1024, 128):
+        check_r_and_q(A, leaf_rows, gram, tol)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("sizes", [(30000,), (8192, 8193, 64, 20000, 1), (70000, 300)])
 def test_batch_leaves_fill_the_device(sizes, dt):
     npdt, gram, _ = DT[dt]
