@@ -303,16 +303,19 @@ struct VSink {
 // registers (ds_bpermute) and forms its own dot product with it locally
 // (lane J's is sigma^2, which all lanes then read from its register), so a
 // step has no cross-lane reduction, and lane k > J updates R1(J, k) and its
-// column.  One wavefront, bound by its chain of NC dependent steps.  Leaves the
-// Householder vectors in v (lane J's column becomes s x, or stays x for an
-// identity reflector) and the tau in tau_out.
-template <typename T, int NC>
+// column.  One wavefront, bound by its chain of NC dependent steps.  With Keep it
+// leaves the Householder vectors in v (lane J's column becomes s x, or stays x for
+// an identity reflector) and the tau in tau_out.
+template <typename T, int NC, bool Keep>
 __device__ __forceinline__ void merge_columns(T (&v)[NC], T* Rs, T* tau_out)
 {
-    const int lane = lane_id();
     static_for<0, NC>([&](auto jc) {
         constexpr int J = decltype(jc)::value;
         constexpr int OFF = Tri<NC>::off(J);
+        // (an opaque copy, so that the compiler does not compute the masks of
+        // all steps ahead and keep them)
+        int lane = lane_id();
+        asm volatile("" : "+v"(lane));
         const bool own = (lane > J) && (lane < NC);
         const int ridx = own ? OFF + lane - J : Tri<NC>::kSize;
         const T alpha = Rs[OFF];
@@ -337,25 +340,31 @@ __device__ __forceinline__ void merge_columns(T (&v)[NC], T* Rs, T* tau_out)
         const T f = own ? h.ts * w : T(0);
 #pragma unroll
         for (int i = 0; i <= J; ++i) v[i] = fmadd(-f, x[i], v[i]);
-        const bool mine = (lane == J) && (h.tau != T(0));
+        if constexpr (Keep) {
+            const bool mine = (lane == J) && (h.tau != T(0));
 #pragma unroll
-        for (int i = 0; i <= J; ++i) v[i] = mine ? h.s * x[i] : v[i];
-        if (lane == 0) tau_out[J] = h.tau;
+            for (int i = 0; i <= J; ++i) v[i] = mine ? h.s * x[i] : v[i];
+            if (lane == 0) tau_out[J] = h.tau;
+        }
         lds_order();
     });
 }
 
-// Column `lane` of a packed NC x NC upper triangle held in LDS (rows packed,
-// buffer padded to Tri<NC>::kPadded elements so every lane's reads stay inside
-// it) into registers, zero below the diagonal and past column NC.
+// Column `lane` of a packed NC x NC upper triangle (LDS or global) into
+// registers, zero below the diagonal and past column NC.
 template <typename T, int NC>
 __device__ __forceinline__ void triangle_column(const T* tri, T (&v)[NC])
 {
-    const int k = lane_id();
+    int k = lane_id();
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-        const T t = tri[k + (Tri<NC>::off(i) - i)];
-        v[i] = (i <= k && k < NC) ? t : T(0);
+        const int at = k + (Tri<NC>::off(i) - i);
+        v[i] = tri[at < Tri<NC>::kSize ? at : Tri<NC>::kSize - 1];
+    }
+    asm volatile("" : "+v"(k));
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        v[i] = (i <= k && k < NC) ? v[i] : T(0);
     }
 }
 
@@ -388,6 +397,64 @@ __device__ __forceinline__ void triangle_to_lds(const T* __restrict__ src, T* ds
 namespace tsqr {
 namespace dev {
 
+// Widths up to which a merge with close columns takes one column per lane
+constexpr int kColumnMerge = 16;
+
+// ---- a merge of the tree ----------------------------------------------------------
+
+// The columns (a bit for each) of the triangle Rs (LDS) that lie mostly in the
+// span of those before them in their panel.  Two triangles of rows that are alike
+// have about this growth in their merge: sum_i R(i, k)^2 over 2 R(k, k)^2.
+template <typename T, int NC>
+__device__ __forceinline__ uint64_t close_columns(const T* Rs)
+{
+    const int lane = lane_id();
+    const int k = lane < NC ? lane : NC - 1;
+    const T* d = Rs + Tri<NC>::off(k);               // R(k - i, k) is i (NC - k) + i (i - 1) / 2 before R(k, k)
+    T sum = T(0);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        const bool in = i <= (k & 3);
+        const T t = d[in ? -(i * (NC - k) + i * (i - 1) / 2) : 0];
+        sum = in ? fmadd(t, t, sum) : sum;
+    }
+    return __builtin_amdgcn_ballot_w64(!(sum <= T(2 * kMaxGrowth) * (d[0] * d[0])));
+}
+
+// Tree node id: Rs := qr([Rs; R2]), Rs packed in LDS, R2 in c as well as, packed,
+// at R2.  Panels that Rs calls close are done one column at a time.  In the narrow
+// widths, where four panels hold little arithmetic, the whole merge is then done
+// with one column per lane, which has the shorter chain; at 50 columns a
+// single close panel would make it the slower way (20001 x 50, six decades,
+// FP64: 279 us, 193 by panels).
+template <typename T, int NC, bool WQ, typename Args>
+__device__ __forceinline__ void merge_node(const Args& a, int id, const T* R2,
+                                           Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work)
+{
+    T* Vn = WQ ? a.qs.Vn + (int64_t)id * Tri<NC>::kSize : nullptr;
+    T* tau = WQ ? a.qs.tau_node + (int64_t)id * NC : nullptr;
+    const uint64_t columns = close_columns<T, NC>(Rs);
+    unsigned close = 0;
+    if (columns != 0) [[unlikely]] {
+        if constexpr (NC <= kColumnMerge) {
+            T v[NC];
+            triangle_column<T, NC>(R2, v);
+            merge_columns<T, NC, WQ>(v, Rs, tau);
+            if constexpr (WQ) {
+                int k = lane_id();
+                asm volatile("" : "+v"(k));
+#pragma unroll
+                for (int i = 0; i < NC; ++i)
+                    if (i <= k && k < NC) Vn[k + (Tri<NC>::off(i) - i)] = v[i];
+            }
+            return;
+        }
+#pragma unroll
+        for (int P = 0; P < Slots<NC>::NS; ++P) close |= (columns >> 4 * P & 15) != 0 ? 1u << P : 0;
+    }
+    merge_panels<T, NC, WQ>(c, Rs, work, close, Vn, tau);
+}
+
 // ---- the fused leaf + tree kernel --------------------------------------------
 
 // Copy a packed triangle from LDS to global memory, the reads first
@@ -409,16 +476,15 @@ __device__ __forceinline__ void triangle_to_global(const T* src, T* __restrict__
 // next chunk's columns into its registers, which no later panel reads.
 template <typename T, int NC, int RPL, bool WQ, typename TIn>
 __device__ __forceinline__ void leaf_chunk(Chunk<T, RPL, Slots<NC>::NS>& c, T* Rs, T* work, int q, int p,
-                                           Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
+                                           unsigned& hard, Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
 {
     static_for<0, Slots<NC>::NS>([&](auto pc) {
         constexpr int P = decltype(pc)::value;
         panel_step<T, NC, RPL, RPL, P, WQ>(
-            c, Rs, work, [&](int rb, T v, const T(&tau)[4], int lo, int hi) {
+            c, Rs, work, hard, [&](int rb, T v, const T(&tau)[4]) {
                 const int k = 4 * P + q;
-                if (k < vs.n && q >= lo && q < hi) vs.V[vs.cbase + 16 * rb + p + (int64_t)k * vs.ldv] = v;
-                if (rb == 0 && lane_id() == 0)
-                    for (int j = lo; j < hi; ++j) vs.tau[4 * P + j] = tau[j];
+                if (k < vs.n) vs.V[vs.cbase + 16 * rb + p + (int64_t)k * vs.ldv] = v;
+                if (rb == 0 && lane_id() < 4 && 4 * P + q < NC) vs.tau[4 * P + q] = of_column(tau, q);
             });
         prefetch_slot<T, RPL, TIn>(c, P, pf);
     });
@@ -454,6 +520,7 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
     // step 1 of the method: the local factorisation of rows [r0, r1)
     if (r1 > r0) {
         C c;
+        unsigned hard = 0;
         wave_sync();
         const int64_t nfull = (r1 - r0) / CH, nchunks = (r1 - r0 + CH - 1) / CH;
         VSink<T> vs{};
@@ -488,7 +555,7 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
                 Prefetch<T, RPL, TIn> pf = make_prefetch<T, RPL, TIn>(
                     a.A, a.lda, more ? a.n : 0, more ? r0 + (t + 1) * CH : 0, q, p);
                 sink(t);
-                leaf_chunk<T, NC, RPL, WQ, TIn>(c, Rs, red, q, p, pf, vs);
+                leaf_chunk<T, NC, RPL, WQ, TIn>(c, Rs, red, q, p, hard, pf, vs);
                 ++t;
             } while (more);
         }
@@ -552,8 +619,8 @@ __device__ __forceinline__ void tree_phase(const LeafTreeArgs<T, TIn>& a, int le
             triangle_to_lds<T, NC>(a.tri + (int64_t)partner * NT, Rs);
         }
         wave_sync();
-        merge_panels<T, NC, WQ>(c, Rs, red, WQ ? a.qs.Vn + (int64_t)id * NT : nullptr,
-                                WQ ? a.qs.tau_node + (int64_t)id * NC : nullptr);
+        // (the right operand is in its slot in either case: its own wavefront put it there)
+        merge_node<T, NC, WQ>(a, id, a.tri + (int64_t)(left + span) * NT, c, Rs, red);
         wave_sync();
         node = left;
         ++level;
@@ -632,16 +699,6 @@ __global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr
     leaf_tree_body<T, NC, RPL, WQ>(a, xcd_local_leaf(blockIdx.x, a.leaves), Rs, red);
 }
 
-// Rs := qr([Rs; R2]), both triangles packed in LDS: tree node id
-template <typename T, int NC, bool WQ>
-__device__ __forceinline__ void merge_lds(const LeafTreeArgs<T>& a, int id, const T* R2, T* Rs, T* work)
-{
-    Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS> c;
-    triangle_chunk<T, NC>(R2, c);
-    merge_panels<T, NC, WQ>(c, Rs, work, WQ ? a.qs.Vn + (int64_t)id * Tri<NC>::kSize : nullptr,
-                            WQ ? a.qs.tau_node + (int64_t)id * NC : nullptr);
-}
-
 // Four leaves per workgroup, one wavefront each (one per SIMD of a compute
 // unit at one wavefront per SIMD): the two lowest tree levels, whose partners
 // then sit in the same workgroup, meet in LDS behind a workgroup barrier
@@ -662,23 +719,25 @@ __global__ void __launch_bounds__(4 * kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) 
     const int base = 4 * xcd_local_leaf(blockIdx.x, (a.leaves + 3) / 4);
     const int leaf = base + w;
     if (leaf < a.leaves) leaf_phase<T, NC, RPL, WQ>(a, leaf, Rs[w], red[w]);
-    __syncthreads();
-    // level 0: leaf base + w (w even) takes base + w + 1 from below
-    if ((w & 1) == 0) {
-        if (leaf + 1 < a.leaves) merge_lds<T, NC, WQ>(a, leaf, Rs[w + 1], Rs[w], red[w]);
-    } else if (a.stamps && leaf < a.leaves && lane_id() == 0) {
-        a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
-        a.stamps[4 * leaf + 3] = 0;
+    // level 0: leaf base + w (w even) takes base + w + 1 from below; level 1:
+    // base takes base + 2.  One copy of the merge's code for both.
+#pragma nounroll
+    for (int level = 0; level < 2; ++level) {
+        const int span = 1 << level;
+        __syncthreads();
+        if ((w & (2 * span - 1)) == 0) {
+            if (leaf + span < a.leaves) {
+                Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS> c;
+                triangle_chunk<T, NC>(Rs[w + span], c);
+                merge_node<T, NC, WQ>(a, leaf + span - 1, Rs[w + span], c, Rs[w], red[w]);
+            }
+        } else if ((w & (span - 1)) == 0 && a.stamps && leaf < a.leaves && lane_id() == 0) {
+            a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
+            a.stamps[4 * leaf + 3] = (uint64_t)level;
+        }
     }
-    __syncthreads();
-    // level 1: base takes base + 2, then the tree goes on through memory
-    if (w == 0) {
-        if (base + 2 < a.leaves) merge_lds<T, NC, WQ>(a, base + 1, Rs[2], Rs[0], red[0]);
-        tree_phase<T, NC, WQ>(a, leaf, base, 2, Rs[0], red[0]);
-    } else if (w == 2 && a.stamps && leaf < a.leaves && lane_id() == 0) {
-        a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
-        a.stamps[4 * leaf + 3] = 1;
-    }
+    // then the tree goes on through memory
+    if (w == 0) tree_phase<T, NC, WQ>(a, leaf, base, 2, Rs[0], red[0]);
 }
 
 // Many independent instances in one launch: workgroup g takes tile
@@ -744,7 +803,7 @@ __global__ void __launch_bounds__(kWave) qr_uppers_kernel(int n, T* R1, T* R2, T
     T v[NC];
     triangle_column<T, NC>(R2s, v);
     wave_sync();
-    merge_columns<T, NC>(v, Rs, taus);
+    merge_columns<T, NC, true>(v, Rs, taus);
     wave_sync();
     for (int idx = lane; idx < n * n; idx += kWave) {
         const int i = idx % n, k = idx / n;

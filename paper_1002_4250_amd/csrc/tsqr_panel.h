@@ -23,12 +23,16 @@
 // Step 2 computes sigma_i^2 from inner products of columns that still contain
 // their components along x_j, j < i, so it loses accuracy by the factor
 //     growth = sum_j (f_i ||x_j||)^2 / (alpha_i^2 + sigma_i^2).
-// Where growth exceeds kMaxGrowth the panel is cut in front of column i: the
-// reflectors found so far are applied to all columns from i on, and the rest of
-// the panel starts again from fresh inner products.  A panel of one column
-// is the plain Householder step, so nothing is assumed about C; the bound only
-// decides how many passes a panel takes (uniform or moderately conditioned
-// columns take one).
+// Where growth exceeds kMaxGrowth, or where a sigma_i^2 came out as no normal
+// number, the result is not used: the panel's own four columns are factored one
+// after the other (panel_columns), each from a fresh sum of squares, and steps 1
+// and 3 are done with the vectors found (panel_trailing).  That is the plain
+// Householder step, so nothing is assumed about C; the bound only decides how
+// much work a panel takes (uniform or moderately conditioned columns never
+// reach it).  Starting again from fresh inner products behind every column whose
+// growth was over the limit, with all other columns carried along, took up to five
+// passes a panel (200001 x 37, eight decades, FP64: 286 us, 227 now; 4000 x 12,
+// six decades: 72 us, 39 now).
 //
 // Register layout.  The matrix instruction is the 4x4x4 FP64 product with four
 // independent blocks, D_b = A_b B_b + C_b.  Writing lane l as 16 d2 + 4 d1 + d0,
@@ -98,6 +102,16 @@ struct Chunk<float, RPL, NS> {
     static __device__ __forceinline__ int p(int lane) { return lane >> 2; }
 };
 
+// Slot s of a chunk as a chunk of its own
+template <typename T, int RB, int NS>
+__device__ __forceinline__ Chunk<T, RB, 1> slot_of(const Chunk<T, RB, NS>& c, int s)
+{
+    Chunk<T, RB, 1> x;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) x.put(r, 0, c.get(r, s));
+    return x;
+}
+
 // LDS work area of one wavefront.  FP64: F (4 rows, stride kFStride so that the
 // four rows read together lie in different banks), then X with d2 and d0
 // exchanged.  FP32: F, the four coefficients of a column together.
@@ -118,12 +132,11 @@ struct MergeRows {
     static constexpr int RB = sizeof(T) == 8 ? (4 * Slots<NC>::NS + 15) / 16 : 4;
 };
 
-// The limit trades passes against accuracy where columns are nearly dependent.
-// 200001 x 37 with singular values over six decades, FP64, three inputs, the
-// largest error of R against an 80-bit reference: limit 16: 232-270 us,
-// 1.1e-15; 10: 276-311 us, 4.7e-16; 8: 302-319 us, 3.3e-16; 4: 346-381 us,
-// 3.1e-16; one column at a time on the vector units: 316 us, 4.6e-16.  Columns of moderate condition never
-// reach any of these.
+// The limit trades accuracy against panels done one column at a time where
+// columns are nearly dependent.  FP64, singular values over six decades: 4000 x 30
+// at limit 10 faster than one column at a time throughout, at 4 slower by 15%;
+// error of R against an 80-bit reference at 4000 x 20 1.15 and 0.83 times that of
+// one column at a time.  Columns of moderate condition never reach either.
 constexpr int kMaxGrowth = 10;
 
 // old with the banks (quads of a 16-lane row) in BANKS replaced by x moved by CTRL
@@ -337,6 +350,36 @@ __device__ __forceinline__ void panel_products(const Chunk<float, RB, NX>& x, co
     }
 }
 
+// x_i . x_j of a panel's columns: entry (i, j) is read from one lane
+template <int RA, int RB>
+__device__ __forceinline__ void panel_gram(const Chunk<double, RB, 1>& x, double (&v)[4])
+{
+    double G = 0.0;
+#pragma unroll
+    for (int rb = 0; rb < RA; ++rb) G = mfma4(x.v[rb][0], x.v[rb][0], G);
+    v[0] = quad_sum(G);
+}
+__device__ __forceinline__ double gram_entry(const double (&v)[4], int i, int j) { return lane_value(v[0], 16 * i + j); }
+
+template <int RA, int RB>
+__device__ __forceinline__ void panel_gram(const Chunk<float, RB, 1>& x, float (&v)[4])
+{
+    float4v G = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int r = 0; r < RA; ++r) G = mfma4((float)x.v[r / 4][0][r % 4], (float)x.v[r / 4][0][r % 4], G);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        float a = quad_sum((float)G[i]), b = a;
+        swap_rows16(a, b);               // the other row of each pair of rows
+        a = a + b;
+        b = a;
+        swap_rows32(a, b);
+        v[i] = a + b;
+    }
+    v[3] = 0.0f;
+}
+__device__ __forceinline__ float gram_entry(const float (&v)[4], int i, int j) { return lane_value(v[i], j); }
+
 // The reflectors of a panel (step 2), one column of [R; C] per lane, the panel's
 // own NJ columns in the lanes from J0 on: g[j] are the inner products of X(:, j)
 // with the lane's column, r[j] the panel's row j of R.
@@ -423,9 +466,11 @@ __device__ __forceinline__ void panel_coefficients(T (&nf)[4], const T (&n)[4][4
 }
 
 // All reflectors of a panel at once.  Returns false, with g and r spoilt, where
-// the panel has to be cut (growth) or a column calls for an identity reflector
-// (one whose sum of squares is below the smallest normal number; a zero
-// column below a zero alpha does no harm here).
+// the panel has to be done one column at a time: growth over the limit, or a
+// sum of squares below the smallest normal number.  A zero column below a zero
+// alpha (every column past n is one) does no harm here: its row of R is zero,
+// and with tau = 0 its reflector is the identity.  With WQ, nf is valid (zero
+// where a reflector does not act) in the lanes of the panel's own columns too.
 template <typename T, int J0, int NJ, bool WQ>
 __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4], int lane)
 {
@@ -451,58 +496,120 @@ __device__ __forceinline__ bool panel_reflectors(T (&g)[4], T (&r)[4], T (&nf)[4
     panel_coefficients<T, NJ>(nf, n);
     bool good = over == 0;
     if (least < Limits<T>::tiny_high) [[unlikely]] {
-        if constexpr (WQ) good = false;   // a stored reflector has to be the identity
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             if (__builtin_amdgcn_ballot_w64(sigma2[j] < Limits<T>::tiny) != 0) {
                 if (__builtin_amdgcn_ballot_w64(sigma2[j] != T(0) || alpha[j] != T(0)) != 0) good = false;
                 r[j] = lane == J0 + j ? alpha[j] : r[j];
+                s[j] = tau[j] = T(0);
             }
     }
     return good;
 }
 
-// The general form: columns below lo are done already; the panel is cut in
-// front of the first column (after lo) whose growth is over the limit, and the
-// result is that column, or NJ.  nf is zero for columns outside [lo, hi); in the
-// lanes of columns left of hi it is valid with WQ only.  A sigma^2 that is not
-// a normal number calls for the identity only where it is a sum of squares as it
-// stands.  After lo it is a difference with an error of about eps grow, and
-// behind one that came out as zero or negative there may be a column of norm
-// sqrt(eps grow), whatever alpha hides in the growth test: the panel is cut
-// there too.
-template <typename T, int J0, int NJ, bool WQ>
-__device__ __forceinline__ int panel_reflectors_cut(T (&g)[4], T (&r)[4], T (&nf)[4], T (&tau)[4], T (&s)[4],
-                                                    int lane, int lo)
+// The sum over the lanes of a column (those that agree in lane & 3), in all of them
+template <typename T>
+__device__ __forceinline__ T column_sum(T x)
 {
-    T n[4][4];
+    T a = quad_sum(x), b = a;
+    swap_rows16(a, b);                   // the other row of each pair of rows
+    a = a + b;
+    b = a;
+    swap_rows32(a, b);
+    return a + b;
+}
+
+// The panel x one column at a time, its first RA row blocks, nj columns: they become the vectors x_j, the panel's own part of R (row0: its
+// first row in LDS, of `row` entries) becomes that of the result, and the
+// scalars z, sgn y and s of reflector j go to work[4 j ..] (the place of F, which
+// is written later).  The result tells whether the growth stayed below the limit and
+// every sum of squares was a normal number, so that all columns at once would
+// have done.  Before step j the columns have been turned by j lanes within
+// their quads, so that one loop body, which finds the pivot column in lane 0 of each
+// quad, serves all four; x_j is fetched twice by DPP rather than kept, which
+// would take the registers that kernels at the limit do not have.
+template <typename T, int RA, int RB>
+__device__ __forceinline__ bool panel_columns(Chunk<T, RB, 1>& c, T* row0, int row, int nj, T* work, int lane)
+{
+#pragma clang fp contract(off)
+    const int q = c.q(lane);
     T grow = T(0);
-    int hi = NJ;
+    bool calm = true;
+    T* Rj = row0;                        // entry (J0 + j, J0 + k) is Rj[k]
+#pragma nounroll
+    for (int j = 0; j < 4; ++j) {
+        if (j < nj) {
+            const int k = (q + j) & 3;   // the lane's column at this step
+            T d = T(0);
+#pragma unroll
+            for (int r = 0; r < RA; ++r) d = fmadd(dpp_mov<0x00>(c.get(r, 0)), c.get(r, 0), d);
+            d = column_sum(d);
+            const T rk = k < row ? Rj[k] : T(0);
+            const T alpha = lane_value(rk, 0), sigma2 = lane_value(d, 0);
+            const T S = fmadd(alpha, alpha, sigma2);
+            PanelScalars<T> h = panel_scalars(alpha, S);
+            const bool normal = __builtin_amdgcn_ballot_w64(sigma2 >= Limits<T>::tiny) != 0;
+            if (!normal) {               // an identity reflector
+                h.z = T(-1);
+                h.sy = T(0);
+                h.beta = alpha;
+            }
+            calm = calm && (__builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) & 1) == 0 &&
+                   (normal || __builtin_amdgcn_ballot_w64(sigma2 != T(0) || alpha != T(0)) == 0);
+            const T s = h.sy * h.q;
+            const T f = k > j ? h.sy * fmadd(s, d, rk) : T(0);
+#pragma unroll
+            for (int r = 0; r < RA; ++r) {
+                T own = c.get(r, 0);
+                asm volatile("" : "+v"(own));
+                const T x = dpp_mov<0x00>(own);
+                c.put(r, 0, fmadd(-f, x, own));
+            }
+            grow = fmadd(f, f * sigma2, grow);
+            if (lane < 4 && k >= j && k < row) Rj[k] = k == j ? h.beta : fmadd(-h.z, rk, -h.sy * d);
+            if (lane == 0) {
+                work[4 * j] = h.z;
+                work[4 * j + 1] = h.sy;
+                work[4 * j + 2] = s;
+            }
+            lds_order();
+            Rj += row - 1 - j;
+        }
+        // quad_perm [1,2,3,0]
+        grow = dpp_mov<0x39>(grow);
+#pragma unroll
+        for (int r = 0; r < RA; ++r) c.put(r, 0, dpp_mov<0x39>(c.get(r, 0)));
+    }
+    return calm;
+}
+
+// The columns after such a panel: their rows of R and the coefficients nf, from
+// the inner products g with its vectors and those among them (v).
+template <typename T, int J0, int NJ>
+__device__ __forceinline__ void panel_trailing(const T* work, const T (&v)[4], T (&g)[4], T (&r)[4], T (&nf)[4],
+                                               T (&tau)[4], T (&s)[4], int lane)
+{
+#pragma clang fp contract(off)
 #pragma unroll
     for (int j = 0; j < 4; ++j) nf[j] = tau[j] = s[j] = T(0);
-    static_for<0, NJ>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        const T alpha = lane_value(r[j], J0 + j);
-        const T sigma2 = lane_value(g[j], J0 + j);
-        const T S = fmadd(alpha, alpha, sigma2);
-        const bool normal = __builtin_amdgcn_ballot_w64(sigma2 >= Limits<T>::tiny) != 0;
-        if constexpr (j > 0) {
-            const uint64_t over = __builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) |
-                                  (normal ? 0 : __builtin_amdgcn_ballot_w64(grow != T(0)));
-            if (((over >> (J0 + j)) & 1) && j > lo && j < hi) hi = j;
-        }
-        PanelScalars<T> h = panel_scalars(alpha, S);
-        if (!normal || j < lo || j >= hi) [[unlikely]] {
-            h.z = T(-1);                  // an identity reflector
-            h.sy = T(0);
-            h.beta = alpha;
-        }
-        s[j] = h.sy * h.q;
-        tau[j] = T(1) + h.z;
-        panel_apply<T, J0, NJ, j, WQ>(h, sigma2, g, r, nf, n, grow, lane);
-    });
-    panel_coefficients<T, NJ>(nf, n);
-    return hi;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const T z = work[4 * j], sy = work[4 * j + 1];
+        s[j] = work[4 * j + 2];
+        tau[j] = T(1) + z;
+        nf[j] = -sy * fmadd(s[j], g[j], r[j]);
+        r[j] = lane < J0 + 4 ? r[j] : fmadd(-z, r[j], -sy * g[j]);
+#pragma unroll
+        for (int i = j + 1; i < NJ; ++i) g[i] = fmadd(nf[j], gram_entry(v, j, i), g[i]);
+    }
+}
+
+// The lane's own column's entry of an array over the panel's columns
+template <typename T>
+__device__ __forceinline__ T of_column(const T (&s)[4], int lane)
+{
+    const int q = lane & 3;
+    return q == 0 ? s[0] : q == 1 ? s[1] : q == 2 ? s[2] : s[3];
 }
 
 // Step 3 of a panel: the columns of slot s (and, for WQ, the panel's own
@@ -526,10 +633,11 @@ struct PanelUpdate<double, RA> {
 #pragma unroll
         for (int j = 0; j < 4; ++j) work[j * kFStride + lane] = nf[j];
     }
+    // X, staged before, in the layout of an A operand
     template <typename C>
-    __device__ __forceinline__ PanelUpdate(const C&, int, const double* work, int lane)
-        : fr(work + (lane >> 4) * kFStride + (lane & 3))
+    __device__ __forceinline__ void fetch(const C&, int, const double* work, int lane)
     {
+        fr = work + (lane >> 4) * kFStride + (lane & 3);
         const double* x = work + 4 * kFStride + x_offset(lane >> 4) + (lane & 15);
 #pragma unroll
         for (int rb = 0; rb < RA; ++rb) xt[rb] = x[rb * kXBlock];
@@ -549,22 +657,12 @@ struct PanelUpdate<double, RA> {
 #pragma unroll
         for (int rb = 0; rb < RA; ++rb) c.v[rb][s - 1] = mfma4(xt[rb], f, c.v[rb][s]);
     }
-    // the panel's own columns from column hi on
-    template <typename C>
-    __device__ __forceinline__ void apply_from(C& c, int s, int lane, int hi) const
-    {
-        double fs = fr[4 * s];
-        asm volatile("" : "+v"(fs));      // read in every lane, no branch around the read
-        const double f = (lane & 3) >= hi ? fs : 0.0;
-#pragma unroll
-        for (int rb = 0; rb < RA; ++rb) c.v[rb][s] = mfma4(xt[rb], f, c.v[rb][s]);
-    }
     // row block rb of the vectors v_j = s_j x_j, x_j = X(:, j) + sum_{i<j} nf_i(J0 + j) X(:, i)
     template <typename Keep>
     __device__ __forceinline__ void reflectors(int P, int lane, const double (&s)[4], Keep&& keep) const
     {
         const int d0 = lane & 3, d2 = lane >> 4;
-        const double sd = d0 == 0 ? s[0] : d0 == 1 ? s[1] : d0 == 2 ? s[2] : s[3];
+        const double sd = of_column(s, lane);
         const double f = d2 < d0 ? fr[4 * P] * sd : (d2 == d0 ? sd : 0.0);
         double v[RA];
 #pragma unroll
@@ -589,9 +687,9 @@ struct PanelUpdate<float, RA> {
         reinterpret_cast<float4v*>(work)[lane] = float4v{nf[0], nf[1], nf[2], nf[3]};
     }
     template <typename C>
-    __device__ __forceinline__ PanelUpdate(const C& c, int P, const float* work, int lane)
-        : fr(reinterpret_cast<const float4v*>(work) + (lane & 3))
+    __device__ __forceinline__ void fetch(const C& c, int P, const float* work, int lane)
     {
+        fr = reinterpret_cast<const float4v*>(work) + (lane & 3);
 #pragma unroll
         for (int r = 0; r < RV; ++r) xt[r] = quad_transpose(c.v[r][P], lane);
     }
@@ -615,21 +713,11 @@ struct PanelUpdate<float, RA> {
 #pragma unroll
             for (int r = 0; r < RV; ++r) c.v[r][s - 1] = mfma4((float)xt[r][k], (float)f[k], c.v[r][s - 1]);
     }
-    template <typename C>
-    __device__ __forceinline__ void apply_from(C& c, int s, int lane, int hi) const
-    {
-        const bool on = (lane & 3) >= hi;
-        const float4v f = fr[4 * s];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int r = 0; r < RV; ++r) c.v[r][s] = mfma4((float)xt[r][k], on ? (float)f[k] : 0.0f, c.v[r][s]);
-    }
     template <typename Keep>
     __device__ __forceinline__ void reflectors(int P, int lane, const float (&s)[4], Keep&& keep) const
     {
         const int j = lane & 3;
-        const float sd = j == 0 ? s[0] : j == 1 ? s[1] : j == 2 ? s[2] : s[3];
+        const float sd = of_column(s, lane);
         const float4v nf = fr[4 * P];
         float4v x[RV];
 #pragma unroll
@@ -647,11 +735,14 @@ struct PanelUpdate<float, RA> {
 };
 
 // One panel, see the top of the file.  Only the first RA row blocks are
-// nonzero in the panel's columns.  keep(rb, v, tau, lo, hi) receives the
-// chunk part of the panel's reflectors where WQ is set: v = s_j x_j in the
-// layout of c, valid for the columns q in [lo, hi).
+// nonzero in the panel's columns.  Bit P of hard, kept from chunk to chunk, is set
+// where the panel was last done one column at a time and its growth called for
+// it: the columns of a matrix that are close to each other are so in every chunk,
+// and the attempt to do them all at once is left out.  keep(rb, v, tau)
+// receives the chunk part of the panel's reflectors where WQ is set: v = s_j x_j
+// in the layout of c.
 template <typename T, int NC, int RB, int RA, int P, bool WQ, typename Keep>
-__device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs, T* work, Keep&& keep)
+__device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs, T* work, unsigned& hard, Keep&& keep)
 {
     constexpr int NS = Slots<NC>::NS;
     constexpr int J0 = 4 * P;
@@ -659,53 +750,67 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
     using Update = PanelUpdate<T, RA>;
     const int lane = lane_id();
     T* Rl = Rs + lane;
-    // lo < 0: all reflectors at once; otherwise from column lo on, with cuts
-    int lo = -1, hi;
-    do {
-        // rows J0.. of R, one column per lane (lanes left of the diagonal and
-        // past NC read other entries of the padded triangle; nothing uses them)
-        T r[4], g[4], nf[4], tau[4], s[4];
+    // rows J0.. of R, one column per lane (lanes left of the diagonal and past
+    // NC read other entries of the padded triangle; nothing uses them)
+    T r[4], g[4], nf[4], tau[4], s[4];
+    auto rows = [&] {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) r[j] = Rl[Tri<NC>::off(J0 + j) - (J0 + j)];
+    };
+    // (the lane passes through an opaque copy so that the compiler does not keep
+    // the masks of every panel alive over the whole chunk)
+    int col = lane;
+    asm volatile("" : "+v"(col));
+    Update up;
+    bool columns = hard >> P & 1;
+    if (!columns) [[likely]] {
+        rows();
         Update::stage(c, P, work, lane);
         lds_order();
         panel_products<P, P, NS, RA>(c, c, g);
-        hi = NJ;
-        // (the lane passes through an opaque copy so that the compiler does not
-        // keep the masks of every panel alive over the whole chunk)
-        int col = lane;
-        asm volatile("" : "+v"(col));
-        if (lo < 0) {
-            if (!panel_reflectors<T, J0, NJ, WQ>(g, r, nf, tau, s, col)) [[unlikely]] {
-                lo = 0;
-                hi = 0;
-                continue;
-            }
-        } else {
-            hi = panel_reflectors_cut<T, J0, NJ, WQ>(g, r, nf, tau, s, col, lo);
-        }
-        // last row first: a lane left of a row's diagonal writes into the end of
-        // the row before, which the next store writes again.
-        if ((unsigned)(col - J0) < (unsigned)(NC - J0)) {
+        columns = !panel_reflectors<T, J0, NJ, WQ>(g, r, nf, tau, s, col);
+        up.fetch(c, P, work, lane);
+    }
+    if (columns) [[unlikely]] {
+        // on a copy of the slot: in FP64 at one wavefront per SIMD the chunk
+        // lies in registers that only the matrix instructions reach, and a panel
+        // that could change it here would be moved out of them in either case
+        // (2^22 x 50: 935 us, 870 as it is)
+        Chunk<T, RB, 1> x = slot_of(c, P);
+        const bool calm = panel_columns<T, RA>(x, Rs + Tri<NC>::off(J0), NC - J0, NJ, work, col);
+        hard = calm ? hard & ~(1u << P) : hard | 1u << P;
+        rows();
+        Update::stage(x, 0, work, lane);
+        lds_order();
+        T v[4];
+        panel_gram<RA>(x, v);
+        if constexpr (P + 1 < NS) panel_products<0, P + 1, NS, RA>(x, c, g);
+        panel_trailing<T, J0, NJ>(work, v, g, r, nf, tau, s, col);
+        up.fetch(x, 0, work, lane);
+        if constexpr (WQ) {
+            const T sd = of_column(s, lane);
 #pragma unroll
-            for (int j = NJ - 1; j >= 0; --j) {
-                Rl[Tri<NC>::off(J0 + j) - (J0 + j)] = r[j];
-                asm volatile("" ::: "memory");
-            }
+            for (int rb = 0; rb < RA; ++rb) keep(rb, sd * x.get(rb, 0), tau);
         }
-        Update::put_f(work, lane, nf);
-        lds_order();
-        const Update up(c, P, work, lane);
-        static_for<P + 1, NS>([&](auto sc) { up.apply(c, decltype(sc)::value); });
-        mfma_settle();
-        if constexpr (WQ) up.reflectors(P, lane, s, [&](int rb, T v) { keep(rb, v, tau, lo < 0 ? 0 : lo, hi); });
-        if (hi < NJ) [[unlikely]] {
-            up.apply_from(c, P, lane, hi);
-            mfma_settle();
+    }
+    // last row first: a lane left of a row's diagonal writes into the end of
+    // the row before, which the next store writes again.
+    if ((unsigned)(col - J0) < (unsigned)(NC - J0)) {
+#pragma unroll
+        for (int j = NJ - 1; j >= 0; --j) {
+            Rl[Tri<NC>::off(J0 + j) - (J0 + j)] = r[j];
+            asm volatile("" ::: "memory");
         }
-        lds_order();
-        lo = hi;
-    } while (hi < NJ);
+    }
+    Update::put_f(work, lane, nf);
+    lds_order();
+    static_for<P + 1, NS>([&](auto sc) { up.apply(c, decltype(sc)::value); });
+    mfma_settle();
+    if constexpr (WQ) {
+        if (!columns) [[likely]]
+            up.reflectors(P, lane, s, [&](int rb, T v) { keep(rb, v, tau); });
+    }
+    lds_order();
 }
 
 // ---- the operator on two triangles ---------------------------------------------
@@ -729,11 +834,12 @@ __device__ __forceinline__ constexpr int merge_first(int rb)
     return sizeof(T) == 8 ? 4 * rb : 0;
 }
 
-// The panels 4 K .. of row block K.  With WQ the reflectors' R2 parts go to Vn
-// (packed by rows) and their tau to tau_out.
+// The panels 4 K .. of row block K.  Panels whose bit is set in close are done one
+// column at a time without an attempt at all four.  With WQ the
+// reflectors' R2 parts go to Vn (packed by rows) and their tau to tau_out.
 template <typename T, int NC, int K, bool WQ>
-__device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work, T* Vn,
-                                                T* tau_out)
+__device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work,
+                                                unsigned close, T* Vn, T* tau_out)
 {
     constexpr int NS = Slots<NC>::NS;
     constexpr int S = NS - 4 * K;                  // live slots at the start
@@ -749,9 +855,8 @@ __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, S
         int at[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) at[j] = __builtin_amdgcn_readfirstlane(Tri<NC>::off(J0 + j) - j);
-        int lo = -1, hi;
-        do {
-            T r[4], g[4], nf[4], tau[4], s[4];
+        T r[4], g[4], nf[4], tau[4], s[4];
+        auto rows = [&] {
 #pragma unroll
             for (int j = 0; j < 4; ++j) r[j] = Rl[at[j]];
             if constexpr (NC % 4 != 0) {
@@ -759,57 +864,65 @@ __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, S
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = lane < NC - J0 && J0 + j < NC ? r[j] : T(0);
             }
+        };
+        [[maybe_unused]] auto keep = [&](int rb, T v) {
+            const int i = 16 * rb + p, k = J0 + q;
+            if (i <= k && k < NC) Vn[Tri<NC>::off(i) + k - i] = v;
+        };
+        Update up;
+        bool columns = close >> P & 1;
+        if (!columns) [[likely]] {
+            rows();
             Update::stage(c, 0, work, lane);
             lds_order();
             panel_products<0, 0, S, RA>(c, c, g);
-            hi = 4;
-            if (lo < 0) {
-                if (!panel_reflectors<T, 0, 4, WQ>(g, r, nf, tau, s, lane)) [[unlikely]] {
-                    lo = 0;
-                    hi = 0;
-                    continue;
-                }
-            } else {
-                hi = panel_reflectors_cut<T, 0, 4, WQ>(g, r, nf, tau, s, lane, lo);
-            }
-            // last row first, as in panel_step
-            if (lane < NC - J0) {
-#pragma unroll
-                for (int j = 3; j >= 0; --j) {
-                    if (NC % 4 == 0 || j < NC % 4 || J0 + j < NC) Rl[at[j]] = r[j];
-                    asm volatile("" ::: "memory");
-                }
-            }
-            Update::put_f(work, lane, nf);
+            columns = !panel_reflectors<T, 0, 4, WQ>(g, r, nf, tau, s, lane);
+            up.fetch(c, 0, work, lane);
+        }
+        if (columns) [[unlikely]] {
+            Chunk<T, MergeRows<T, NC>::RB, 1> x = slot_of(c, 0);
+            panel_columns<T, RA>(x, Rs + at[0], NC - J0, NC - J0 < 4 ? NC - J0 : 4, work, lane);
+            rows();
+            Update::stage(x, 0, work, lane);
             lds_order();
-            const Update up(c, 0, work, lane);
+            T v[4];
+            panel_gram<RA>(x, v);
+            if constexpr (S > 1) panel_products<0, 1, S, RA>(x, c, g);
+            panel_trailing<T, 0, 4>(work, v, g, r, nf, tau, s, lane);
+            up.fetch(x, 0, work, lane);
             if constexpr (WQ) {
-                up.reflectors(0, lane, s, [&](int rb, T v) {
-                    const int i = 16 * rb + p, k = J0 + q;
-                    if (i <= k && k < NC && q >= lo && q < hi) Vn[Tri<NC>::off(i) + k - i] = v;
-                });
-                if (lane < 4 && lane >= lo && lane < hi && J0 + lane < NC)
-                    tau_out[J0 + lane] = lane == 0 ? tau[0] : lane == 1 ? tau[1] : lane == 2 ? tau[2] : tau[3];
+                const T sd = of_column(s, lane);
+#pragma unroll
+                for (int rb = 0; rb < RA; ++rb) keep(rb, sd * x.get(rb, 0));
             }
-            if (hi < 4) [[unlikely]] {
-                static_for<1, S>([&](auto sc) { up.apply(c, decltype(sc)::value); });
-                up.apply_from(c, 0, lane, hi);
-            } else {
-                static_for<1, S>([&](auto sc) { up.apply_shift(c, decltype(sc)::value); });
+        }
+        // last row first, as in panel_step
+        if (lane < NC - J0) {
+#pragma unroll
+            for (int j = 3; j >= 0; --j) {
+                if (NC % 4 == 0 || j < NC % 4 || J0 + j < NC) Rl[at[j]] = r[j];
+                asm volatile("" ::: "memory");
             }
-            mfma_settle();
-            lds_order();
-            lo = hi;
-        } while (hi < 4);
+        }
+        Update::put_f(work, lane, nf);
+        lds_order();
+        if constexpr (WQ) {
+            if (!columns) [[likely]]
+                up.reflectors(0, lane, s, keep);
+            if (lane < 4 && J0 + lane < NC) tau_out[J0 + lane] = of_column(tau, lane);
+        }
+        static_for<1, S>([&](auto sc) { up.apply_shift(c, decltype(sc)::value); });
+        mfma_settle();
+        lds_order();
     }
 }
 
 template <typename T, int NC, bool WQ>
-__device__ __forceinline__ void merge_panels(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work, T* Vn,
-                                             T* tau_out)
+__device__ __forceinline__ void merge_panels(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work,
+                                             unsigned close, T* Vn, T* tau_out)
 {
     static_for<0, (Slots<NC>::NS + 3) / 4>(
-        [&](auto kc) { merge_row_block<T, NC, decltype(kc)::value, WQ>(c, Rs, work, Vn, tau_out); });
+        [&](auto kc) { merge_row_block<T, NC, decltype(kc)::value, WQ>(c, Rs, work, close, Vn, tau_out); });
 }
 
 // The triangle tri (packed by rows, LDS or global) as the bottom operand of

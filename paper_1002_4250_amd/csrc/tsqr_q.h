@@ -66,36 +66,6 @@ __device__ __forceinline__ void zero_spare_rows(T* top)
     for (int j = NC; j < 4 * Slots<NC>::NS; ++j) top[j * kTopStride + lane_id()] = T(0);
 }
 
-// v_i . v_j of the panel's columns: entry (i, j) is read from one lane
-template <int RA, int RB>
-__device__ __forceinline__ void panel_gram(const Chunk<double, RB, 1>& x, double (&v)[4])
-{
-    double G = 0.0;
-#pragma unroll
-    for (int rb = 0; rb < RA; ++rb) G = mfma4(x.v[rb][0], x.v[rb][0], G);
-    v[0] = quad_sum(G);
-}
-__device__ __forceinline__ double gram_entry(const double (&v)[4], int i, int j) { return lane_value(v[0], 16 * i + j); }
-
-template <int RA, int RB>
-__device__ __forceinline__ void panel_gram(const Chunk<float, RB, 1>& x, float (&v)[4])
-{
-    float4v G = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int r = 0; r < RA; ++r) G = mfma4((float)x.v[r / 4][0][r % 4], (float)x.v[r / 4][0][r % 4], G);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        float a = quad_sum((float)G[i]), b = a;
-        swap_rows16(a, b);               // the other row of each pair of rows
-        a = a + b;
-        b = a;
-        swap_rows32(a, b);
-        v[i] = a + b;
-    }
-    v[3] = 0.0f;
-}
-__device__ __forceinline__ float gram_entry(const float (&v)[4], int i, int j) { return lane_value(v[i], j); }
-
 // The four reflectors from column J0 on, X in x (its first RA row blocks), applied to
 // the stack [T; C]: T in LDS (rows of kTopStride), C the KS slots of c.  Forward:
 // H_0 first (Q^T); otherwise H_3 first (Q).  Lane J of taus holds tau_J (zero past
@@ -134,7 +104,8 @@ __device__ __forceinline__ void apply_panel(int J0, const Chunk<T, RB, 1>& x, Ch
     for (int j = 0; j < 4; ++j) y[j] = -y[j];
     Update::put_f(work, lane, y);
     lds_order();
-    const Update up(x, 0, work, lane);
+    Update up;
+    up.fetch(x, 0, work, lane);
     static_for<0, KS>([&](auto sc) { up.apply(c, decltype(sc)::value); });
     mfma_settle();
     lds_order();

@@ -1,9 +1,9 @@
 """The four-column panels of the leaves, merges and Q passes, and the Gram pass
 of the mixed-precision correction, at the sizes where they can go wrong: the
-edges of the compiled column widths (8, 24, 40 among them), one to five leaves
+edges of the compiled column widths (8, 24, 40 among them), one to seven leaves
 (one launch without counters up to four, the last group partly filled, the
 first tree level through memory), a ragged last chunk, panels that have to be
-cut, leaves cut shorter so that a batch fills the device, and row counts around
+done one column at a time, leaves cut shorter so that a batch fills the device, and row counts around
 the 16-row tiles of the Gram pass.
 
 Tolerances: the backward-error gates of ``gates`` (they hold at any condition
@@ -125,6 +125,21 @@ def test_zero_column_under_a_diagonal(n, dt):
         A[128:, j] = 0
     for leaf_rows in (1024, 128):
         check_r_and_q(A, leaf_rows, gram, tol)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n", [5, 12, 16, 20, 41, 50, 64])
+@pytest.mark.parametrize("leaf_rows", [1024, 256, 128])
+def test_close_columns_in_some_chunks(n, leaf_rows, dt):
+    """Panels done one column at a time, in leaves (where that is kept from chunk
+    to chunk until the columns are apart again) and in merges of triangles that
+    are both close, or one of them."""
+    npdt, gram, tol = DT[dt]
+    rng = np.random.default_rng(n)
+    V, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    close = rng.uniform(-1, 1, (384, n)) * (10.0 ** (-(6 if dt == "f64" else 3) * np.arange(n) / n)) @ V.T
+    A = np.concatenate([close, rng.uniform(-1, 1, (391, n)), close[:250]])
+    check_r_and_q(np.asfortranarray(A.astype(npdt)), leaf_rows, gram, tol)
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
