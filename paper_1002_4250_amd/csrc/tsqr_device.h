@@ -61,6 +61,14 @@ struct Slots {
     static constexpr int NS = (NC + 3) / 4;     // column slots per lane
 };
 
+// The smallest column count that runs at a width: panels that begin before it always
+// hold a column.  (33 to 40 columns run at 50 with a number of rows per lane that
+// the width 40 is not compiled for.)
+template <int NC>
+constexpr int kMinColumns = NC <= 8 ? 1 : NC <= 16 ? 9 : NC <= 24 ? 17 : NC <= 32 ? 25 : NC <= 50 ? 33 : 51;
+// The panels of n columns
+__device__ __forceinline__ int panels_of(int n) { return (n + 3) / 4; }
+
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F&& f)
 {
@@ -290,7 +298,6 @@ struct VSink {
     int64_t ldv;
     T* tau;
     int64_t cbase;    // first row of the chunk
-    int n;
 };
 
 // ---- the operator with one column per lane -------------------------------------
@@ -307,10 +314,11 @@ struct VSink {
 // leaves the Householder vectors in v (lane J's column becomes s x, or stays x for
 // an identity reflector) and the tau in tau_out.
 template <typename T, int NC, bool Keep>
-__device__ __forceinline__ void merge_columns(T (&v)[NC], T* Rs, T* tau_out)
+__device__ __forceinline__ void merge_columns(T (&v)[NC], T* Rs, T* tau_out, int n = NC)
 {
     static_for<0, NC>([&](auto jc) {
         constexpr int J = decltype(jc)::value;
+        if (J >= kMinColumns<NC> && J >= n) return;
         constexpr int OFF = Tri<NC>::off(J);
         // (an opaque copy, so that the compiler does not compute the masks of
         // all steps ahead and keep them)
@@ -439,7 +447,7 @@ __device__ __forceinline__ void merge_node(const Args& a, int id, const T* R2,
         if constexpr (NC <= kColumnMerge) {
             T v[NC];
             triangle_column<T, NC>(R2, v);
-            merge_columns<T, NC, WQ>(v, Rs, tau);
+            merge_columns<T, NC, WQ>(v, Rs, tau, a.n);
             if constexpr (WQ) {
                 int k = lane_id();
                 asm volatile("" : "+v"(k));
@@ -452,7 +460,7 @@ __device__ __forceinline__ void merge_node(const Args& a, int id, const T* R2,
 #pragma unroll
         for (int P = 0; P < Slots<NC>::NS; ++P) close |= (columns >> 4 * P & 15) != 0 ? 1u << P : 0;
     }
-    merge_panels<T, NC, WQ>(c, Rs, work, close, Vn, tau);
+    merge_panels<T, NC, WQ>(c, Rs, work, a.n, close, Vn, tau);
 }
 
 // ---- the fused leaf + tree kernel --------------------------------------------
@@ -473,19 +481,22 @@ __device__ __forceinline__ void triangle_to_global(const T* src, T* __restrict__
 }
 
 // One chunk of a leaf: the panels in order, each followed by the loads of the
-// next chunk's columns into its registers, which no later panel reads.
+// next chunk's columns into its registers, which no later panel reads.  Panels
+// past column n are left out (333333 x 20, Q and R in FP32: 286 us with them, 264
+// without); their loads are not, so that their number is known.
 template <typename T, int NC, int RPL, bool WQ, typename TIn>
 __device__ __forceinline__ void leaf_chunk(Chunk<T, RPL, Slots<NC>::NS>& c, T* Rs, T* work, int q, int p,
-                                           unsigned& hard, Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
+                                           int n, unsigned& hard, Prefetch<T, RPL, TIn>& pf, const VSink<T>& vs)
 {
     static_for<0, Slots<NC>::NS>([&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        panel_step<T, NC, RPL, RPL, P, WQ>(
-            c, Rs, work, hard, [&](int rb, T v, const T(&tau)[4]) {
-                const int k = 4 * P + q;
-                if (k < vs.n) vs.V[vs.cbase + 16 * rb + p + (int64_t)k * vs.ldv] = v;
-                if (rb == 0 && lane_id() < 4 && 4 * P + q < NC) vs.tau[4 * P + q] = of_column(tau, q);
-            });
+        if (4 * P < kMinColumns<NC> || 4 * P < n)
+            panel_step<T, NC, RPL, RPL, P, WQ>(
+                c, Rs, work, hard, [&](int rb, T v, const T(&tau)[4]) {
+                    const int k = 4 * P + q;
+                    if (k < n) vs.V[vs.cbase + 16 * rb + p + (int64_t)k * vs.ldv] = v;
+                    if (rb == 0 && lane_id() < 4 && 4 * P + q < NC) vs.tau[4 * P + q] = of_column(tau, q);
+                });
         prefetch_slot<T, RPL, TIn>(c, P, pf);
     });
 }
@@ -529,7 +540,6 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
                 vs.V = a.qs.V;
                 vs.ldv = a.qs.ldv;
                 vs.cbase = r0 + t * CH;
-                vs.n = a.n;
                 vs.tau = a.qs.tau_leaf + (vs.cbase / CH) * NC;
             }
         };
@@ -555,7 +565,7 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
                 Prefetch<T, RPL, TIn> pf = make_prefetch<T, RPL, TIn>(
                     a.A, a.lda, more ? a.n : 0, more ? r0 + (t + 1) * CH : 0, q, p);
                 sink(t);
-                leaf_chunk<T, NC, RPL, WQ, TIn>(c, Rs, red, q, p, hard, pf, vs);
+                leaf_chunk<T, NC, RPL, WQ, TIn>(c, Rs, red, q, p, a.n, hard, pf, vs);
                 ++t;
             } while (more);
         }

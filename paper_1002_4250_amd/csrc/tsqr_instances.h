@@ -25,7 +25,9 @@
 // Column counts with a compiled kernel (ascending).  The work of a chunk grows
 // with the square of the compiled width and its dependent chain with the width
 // itself, so a column count runs at the next width that has the plan's rows per
-// lane: 37 columns as 40, not as 50.
+// lane: 37 columns as 40, not as 50 (unless the launch table asks for rows per
+// lane that only 50 is compiled for).  Panels of a width past the last column
+// are left out.
 #define TSQR_NC_VALUES 8, 16, 24, 32, 40, 50, 64
 #define TSQR_FOR_EACH_NC(N) N(8) N(16) N(24) N(32) N(40) N(50) N(64)
 // the widths of the tuning table (an entry applies to every column count up to

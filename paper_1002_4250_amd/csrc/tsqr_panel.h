@@ -834,12 +834,12 @@ __device__ __forceinline__ constexpr int merge_first(int rb)
     return sizeof(T) == 8 ? 4 * rb : 0;
 }
 
-// The panels 4 K .. of row block K.  Panels whose bit is set in close are done one
+// The panels 4 K .. of row block K that hold a column before n.  Panels whose bit is set in close are done one
 // column at a time without an attempt at all four.  With WQ the
 // reflectors' R2 parts go to Vn (packed by rows) and their tau to tau_out.
 template <typename T, int NC, int K, bool WQ>
 __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work,
-                                                unsigned close, T* Vn, T* tau_out)
+                                                int n, unsigned close, T* Vn, T* tau_out)
 {
     constexpr int NS = Slots<NC>::NS;
     constexpr int S = NS - 4 * K;                  // live slots at the start
@@ -849,7 +849,7 @@ __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, S
     const int q = c.q(lane), p = c.p(lane);
     T* Rl = Rs + lane;
 #pragma nounroll
-    for (int P = 4 * K; P < (S < 4 ? NS : 4 * K + 4); ++P) {
+    for (int P = 4 * K; P < (S < 4 ? NS : 4 * K + 4) && 4 * P < n; ++P) {
         const int J0 = 4 * P;
         // offset of entry (J0 + j, J0 + lane) of the packed triangle, without the lane
         int at[4];
@@ -919,10 +919,10 @@ __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, S
 
 template <typename T, int NC, bool WQ>
 __device__ __forceinline__ void merge_panels(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c, T* Rs, T* work,
-                                             unsigned close, T* Vn, T* tau_out)
+                                             int n, unsigned close, T* Vn, T* tau_out)
 {
     static_for<0, (Slots<NC>::NS + 3) / 4>(
-        [&](auto kc) { merge_row_block<T, NC, decltype(kc)::value, WQ>(c, Rs, work, close, Vn, tau_out); });
+        [&](auto kc) { merge_row_block<T, NC, decltype(kc)::value, WQ>(c, Rs, work, n, close, Vn, tau_out); });
 }
 
 // The triangle tri (packed by rows, LDS or global) as the bottom operand of

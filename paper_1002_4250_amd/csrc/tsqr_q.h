@@ -136,14 +136,15 @@ __device__ __forceinline__ void node_reflectors(Chunk<T, RB, 1>& x, const T* Vl,
     }
 }
 
-// All reflectors of a merge applied to [T; C].  The panels of the first two row
-// blocks leave the other rows alone.
+// All reflectors of a merge of n columns applied to [T; C].  The panels of the first
+// two row blocks leave the other rows alone.
 template <typename T, int NC, int KS, bool Forward>
 __device__ __forceinline__ void apply_node(Chunk<T, MergeRows<T, NC>::RB, KS>& c, const T* Vl, T* top, T* work, T tau,
-                                           int q, int p)
+                                           int n, int q, int p)
 {
     constexpr int RB = MergeRows<T, NC>::RB, NS = Slots<NC>::NS;
     constexpr int RL = RB < 2 ? RB : 2, PL = NS < 8 ? NS : 8;
+    const int np = panels_of(n);
     auto part = [&](auto rows, int first, int last) {
 #pragma nounroll
         for (int i = first; i < last; ++i) {
@@ -153,9 +154,9 @@ __device__ __forceinline__ void apply_node(Chunk<T, MergeRows<T, NC>::RB, KS>& c
             apply_panel<T, RB, decltype(rows)::value, KS, Forward>(4 * P, x, c, top, work, tau);
         }
     };
-    if constexpr (!Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, NS);
-    part(std::integral_constant<int, RL>{}, 0, PL);
-    if constexpr (Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, NS);
+    if constexpr (!Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, np);
+    part(std::integral_constant<int, RL>{}, 0, np < PL ? np : PL);
+    if constexpr (Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, np);
 }
 
 // Level `level` of the tree, root first: workgroup g takes the merge whose
@@ -187,7 +188,7 @@ __global__ void __launch_bounds__(kWave) q_tree_kernel(LeafTreeArgs<T> a, int le
     for (int r = 0; r < RB; ++r)
 #pragma unroll
         for (int s = 0; s < NS; ++s) c.put(r, s, T(0));
-    apply_node<T, NC, NS, false>(c, Vl, top, work, tau, q, p);
+    apply_node<T, NC, NS, false>(c, Vl, top, work, tau, a.n, q, p);
     wave_sync();
     store_top<T, NC, NC, NC>(top, qL);
 #pragma unroll
@@ -223,7 +224,7 @@ __global__ void __launch_bounds__(kWave) q_leaf_kernel(LeafTreeArgs<T> a, T* Q, 
     if (r1 <= r0) return;
     const int64_t nchunks = (r1 - r0 + CH - 1) / CH;
     // panels past n hold no reflectors; the last one that does comes first
-    const int plast = (n - 1) / 4;
+    const int plast = panels_of(n) - 1;
     const int64_t c0 = r0 / CH;                  // the leaf's first chunk among all
     auto taus = [&](int64_t t) { return lane < NC ? a.qs.tau_leaf[(c0 + t) * NC + lane] : T(0); };
     Chunk<T, RPL, 1> x, nx;
@@ -294,7 +295,7 @@ __global__ void __launch_bounds__(kWave) qt_leaf_kernel(QtArgs<T> x)
     zero_spare_rows<T, NC>(top);
     wave_sync();
     const int64_t nchunks = r1 > r0 ? (r1 - r0 + CH - 1) / CH : 0;
-    const int plast = (n - 1) / 4;
+    const int plast = panels_of(n) - 1;
     const int64_t c0 = r0 / CH;                  // the leaf's first chunk among all
     auto taus = [&](int64_t t) { return lane < NC ? a.qs.tau_leaf[(c0 + t) * NC + lane] : T(0); };
     // a chunk's rows of B; the next chunk's are loaded a chunk ahead where the
@@ -376,7 +377,7 @@ __global__ void __launch_bounds__(kWave) qt_tree_kernel(QtArgs<T> x, int level)
             c.put(r, s, row < NC ? tr[row * kQtCols + 4 * s + q] : T(0));
         }
     wave_sync();
-    apply_node<T, NC, KS, true>(c, Vl, top, work, tau, q, p);
+    apply_node<T, NC, KS, true>(c, Vl, top, work, tau, a.n, q, p);
     wave_sync();
     store_top<T, NC, 4 * KS, kQtCols>(top, tl);
 }

@@ -64,6 +64,21 @@ def check_r_and_q(A, leaf_rows, gram, tol, orthogonal=True):
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n", [4, 5, 9, 12, 13, 17, 20, 21, 28, 33, 36, 37, 44, 45, 48, 51, 52, 57, 60])
+def test_panels_past_the_last_column(n, dt):
+    """Counts that leave panels of their width without a column, in leaves, merges
+    and Q passes; the workspace holds NaN where nothing is written."""
+    npdt, gram, tol = DT[dt]
+    A = inputs.uniform(900, n, 800 + n, npdt)
+    check_r_and_q(A, 128, gram, tol)
+    h, Ad = tsqr.handle(0), to_dev(A)
+    nbytes = tsqr.tsqr_qr_workspace_bytes(h, 900, n, tsqr.TSQR_F64 if dt == "f64" else tsqr.TSQR_F32)
+    ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
+    Q, R = (x.cpu().numpy().astype(np.float64) for x in tsqr.geqr_qr(Ad, ws=ws))
+    assert relF(Q @ R, A.astype(np.float64)) < tol
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("n,leaves", [(8, 1), (8, 3), (9, 2), (24, 4), (24, 5), (25, 1), (40, 2), (40, 5), (41, 3),
                                       (41, 4), (3, 5), (64, 3), (50, 7)])
 def test_widths_and_leaf_counts(n, leaves, dt):
