@@ -531,7 +531,10 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
     // step 1 of the method: the local factorisation of rows [r0, r1)
     if (r1 > r0) {
         C c;
-        unsigned hard = 0;
+        // Behind as many columns as the leaf has rows, rounding errors are left of
+        // the others: those panels cannot be done at once (129 x 45 in
+        // FP64: 73 us with the attempt, 61 without; 775 x 45 in FP32: 89 and 78)
+        unsigned hard = r1 - r0 < a.n ? ~0u << ((int)(r1 - r0) / 4) : 0;
         wave_sync();
         const int64_t nfull = (r1 - r0) / CH, nchunks = (r1 - r0 + CH - 1) / CH;
         VSink<T> vs{};
