@@ -590,17 +590,22 @@ int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m,
     if (n > 0 && leaf_rows > 0) {
         L = align_up(leaf_rows, (int64_t)kRowsPerLaneUnit * g.rpl);
     } else if (n > 0 && fill && !h->planning_only && h->leaf_rows == 0 && !find_tuning(h, dtype, padded_columns(n), 1, true)) {
-        // a batch that does not fill the device with leaves of 64 chunks lasts
-        // as long as its longest leaf while the other compute units are idle:
-        // cut it into as many leaves as are resident at once (512 instances of
-        // 8 to 20000 rows, n = 32, FP64: 397 us, 674 us with 64 chunks).  The planning
-        // handle, which has no device to fill, keeps 64 chunks.
-        int64_t rows = 0;
-        for (int64_t b = 0; b < batch && rows < (int64_t)1 << 60; ++b) rows += std::min(m[b], (int64_t)1 << 60);
-        const int64_t target = (int64_t)h->cu_count * leaf_occupancy(h, dtype, g.nc, g.rpl);
+        // A batch lasts as long as its longest leaf, c chunks after each other, or
+        // as all its leaves' handoffs, whose fences meet in the caches: with T
+        // chunks in all the two are balanced at c ~ sqrt(T), less where a chunk
+        // takes longer.  More leaves than are resident at once never help.  The
+        // factor is measured on ragged batches of 3 10^3 to 4 10^6 rows, n = 1 to
+        // 64, both types.  FP32, n = 8, 1000 of 16 to 1000 rows: 16 us (86 with as
+        // many leaves as are resident, 16 with 64 chunks); 100 of 64 to
+        // 65536 rows: 71 (633, 120); FP64, n = 32, 512 of 8 to 20000 rows: 230
+        // (352, 686); n = 50, 1000 of 500 to 16000 rows: 854 (854, 1372).  The
+        // planning handle, which has no device to fill, keeps 64 chunks.
         const int64_t chunk = (int64_t)kRowsPerLaneUnit * g.rpl;
-        const int64_t even = align_up(std::max((rows + target - 1) / target, chunk), chunk);
-        L = std::min(L, even);
+        const double slots = (double)h->cu_count * leaf_occupancy(h, dtype, g.nc, g.rpl);
+        double T = 0;
+        for (int64_t b = 0; b < batch; ++b) T += (double)m[b] / (double)chunk;
+        const double c = std::ceil(std::max(std::sqrt(T) / (4 + g.nc / 8.0), T / std::max(slots, 1.0)));
+        if (c * (double)chunk < (double)L) L = chunk * std::max<int64_t>((int64_t)c, 1);
     }
     std::vector<tsqr::BatchInstance> inst((size_t)batch);
     std::vector<tsqr::BatchTile> tiles;
