@@ -545,9 +545,12 @@ struct tsqr_batch_plan_s {
 };
 
 namespace {
+// Where a batch's leaf size follows the batch: nowhere (the fallback, whose size
+// is the workspace's), unless the handle's option or table gives one, or in any case
+enum class LeafRule { kNever, kUntuned, kAlways };
 int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m, const int64_t* a_offset,
                     const int64_t* lda, int dtype, int force_rpl, tsqr_batch_plan_t* out,
-                    int64_t leaf_rows = 0, bool fill = true);
+                    LeafRule rule = LeafRule::kUntuned);
 }
 
 int tsqr_batch_plan_create(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m, const int64_t* a_offset,
@@ -559,11 +562,9 @@ int tsqr_batch_plan_create(tsqr_handle_t h, int64_t batch, int64_t n, const int6
 namespace {
 // The batched plan; force_rpl (if positive) fixes the rows per lane, as the
 // mixed-precision fallback (compiled at 8 rows per lane only) needs, and
-// leaf_rows (if positive) the leaf size, rounded up to whole chunks.  `fill`
-// lets the leaf size follow the batch (see below).
+// `rule` says where the leaf size follows the batch (see below).
 int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m, const int64_t* a_offset,
-                    const int64_t* lda, int dtype, int force_rpl, tsqr_batch_plan_t* out, int64_t leaf_rows,
-                    bool fill)
+                    const int64_t* lda, int dtype, int force_rpl, tsqr_batch_plan_t* out, LeafRule rule)
 {
     if (!h) return -1;
     if (batch < 0) return -2;
@@ -587,9 +588,9 @@ int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m,
     // entry, else 64 chunks (see plan)
     int64_t L = n > 0 ? g.leaf_rows
                       : (h->leaf_rows > 0 ? align_up(h->leaf_rows, kRowsPerLaneUnit) : 64 * kRowsPerLaneUnit);
-    if (n > 0 && leaf_rows > 0) {
-        L = align_up(leaf_rows, (int64_t)kRowsPerLaneUnit * g.rpl);
-    } else if (n > 0 && fill && !h->planning_only && h->leaf_rows == 0 && !find_tuning(h, dtype, padded_columns(n), 1, true)) {
+    if (n > 0 && (rule == LeafRule::kAlways ||
+                  (rule == LeafRule::kUntuned && !h->planning_only && h->leaf_rows == 0 &&
+                   !find_tuning(h, dtype, padded_columns(n), 1, true)))) {
         // A batch lasts as long as its longest leaf, c chunks after each other, or
         // as all its leaves' handoffs, whose fences meet in the caches: with T
         // chunks in all the two are balanced at c ~ sqrt(T), less where a chunk
@@ -605,6 +606,7 @@ int batch_plan_make(tsqr_handle_t h, int64_t batch, int64_t n, const int64_t* m,
         double T = 0;
         for (int64_t b = 0; b < batch; ++b) T += (double)m[b] / (double)chunk;
         const double c = std::ceil(std::max(std::sqrt(T) / (4 + g.nc / 8.0), T / std::max(slots, 1.0)));
+        if (rule == LeafRule::kAlways) L = 64 * chunk;
         if (c * (double)chunk < (double)L) L = chunk * std::max<int64_t>((int64_t)c, 1);
     }
     std::vector<tsqr::BatchInstance> inst((size_t)batch);
@@ -885,12 +887,14 @@ int mixed_plan_make(tsqr_handle_t h, int64_t batch, int64_t m, int64_t n, int64_
     std::vector<int64_t> fms((size_t)batch, m), foffs((size_t)batch), fldas((size_t)batch, lda);
     for (int64_t b = 0; b < batch; ++b) foffs[(size_t)b] = b * stride_a;
     tsqr_batch_plan_t inner = nullptr, fb = nullptr;
-    // a sample is short: its leaves are sized so the batch has about 2048 of
-    // them (every SIMD busy) instead of the batched default
-    const int64_t sample_leaf = srows ? (batch * srows + 2047) / 2048 : 0;
-    int rc = batch_plan_make(h, batch, n, ms.data(), offs.data(), ldas.data(), TSQR_F32, 0, &inner, sample_leaf);
+    // a sample is short: no option or table that was made for whole batches
+    // sizes its leaves (about 2048 of them in all, as many as there are SIMDs
+    // for, made it wait for their handoffs: 32 x 10000 x 8 with samples of 4096 rows
+    // 131 us, 59 as it is)
+    int rc = batch_plan_make(h, batch, n, ms.data(), offs.data(), ldas.data(), TSQR_F32, 0, &inner,
+                             srows ? LeafRule::kAlways : LeafRule::kUntuned);
     if (rc) return rc;
-    rc = batch_plan_make(h, batch, n, fms.data(), foffs.data(), fldas.data(), TSQR_F64, 8, &fb, 0, false);
+    rc = batch_plan_make(h, batch, n, fms.data(), foffs.data(), fldas.data(), TSQR_F64, 8, &fb, LeafRule::kNever);
     if (rc) {
         tsqr_batch_plan_destroy(inner);
         return rc;
