@@ -857,8 +857,12 @@ __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, S
     const int lane = lane_id();
     const int q = c.q(lane), p = c.p(lane);
     T* Rl = Rs + lane;
+    const int end = S < 4 ? NS : 4 * K + 4, last = panels_of(n) < end ? panels_of(n) : end;
+    int P = 4 * K;
+    if (4 * P >= kMinColumns<NC> && P >= last) return;
+    // (once at least: registers that a loop may leave as they are get copied)
 #pragma nounroll
-    for (int P = 4 * K; P < (S < 4 ? NS : 4 * K + 4) && 4 * P < n; ++P) {
+    do {
         const int J0 = 4 * P;
         // offset of entry (J0 + j, J0 + lane) of the packed triangle, without the lane
         int at[4];
@@ -923,7 +927,7 @@ __device__ __forceinline__ void merge_row_block(Chunk<T, MergeRows<T, NC>::RB, S
         static_for<1, S>([&](auto sc) { up.apply_shift(c, decltype(sc)::value); });
         mfma_settle();
         lds_order();
-    }
+    } while (++P < last);
 }
 
 template <typename T, int NC, bool WQ>

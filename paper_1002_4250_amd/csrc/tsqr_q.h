@@ -145,18 +145,23 @@ __device__ __forceinline__ void apply_node(Chunk<T, MergeRows<T, NC>::RB, KS>& c
     constexpr int RB = MergeRows<T, NC>::RB, NS = Slots<NC>::NS;
     constexpr int RL = RB < 2 ? RB : 2, PL = NS < 8 ? NS : 8;
     const int np = panels_of(n);
+    // (at least one panel: registers that a loop may leave as they are get copied)
     auto part = [&](auto rows, int first, int last) {
+        int i = first;
 #pragma nounroll
-        for (int i = first; i < last; ++i) {
+        do {
             const int P = Forward ? i : first + last - 1 - i;
             Chunk<T, RB, 1> x;
             node_reflectors<T, NC>(x, Vl, P, q, p);
             apply_panel<T, RB, decltype(rows)::value, KS, Forward>(4 * P, x, c, top, work, tau);
-        }
+        } while (++i < last);
     };
-    if constexpr (!Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, np);
+    const bool more = NS > PL && (4 * PL < kMinColumns<NC> || np > PL);
+    if constexpr (!Forward && NS > PL)
+        if (more) part(std::integral_constant<int, RB>{}, PL, np);
     part(std::integral_constant<int, RL>{}, 0, np < PL ? np : PL);
-    if constexpr (Forward && NS > PL) part(std::integral_constant<int, RB>{}, PL, np);
+    if constexpr (Forward && NS > PL)
+        if (more) part(std::integral_constant<int, RB>{}, PL, np);
 }
 
 // Level `level` of the tree, root first: workgroup g takes the merge whose
