@@ -429,6 +429,50 @@ __device__ __forceinline__ uint64_t close_columns(const T* Rs)
     return __builtin_amdgcn_ballot_w64(!(sum <= T(2 * kMaxGrowth) * (d[0] * d[0])));
 }
 
+// Whether R2 holds a NaN or an infinity
+template <typename T, int RB, int NS>
+__device__ __forceinline__ bool not_finite(const Chunk<T, RB, NS>& c)
+{
+    T t = T(0);
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) t = fmadd(c.get(r, s), T(0), t);
+    return __builtin_amdgcn_ballot_w64(!(t == T(0))) != 0;
+}
+
+// Such an R2 for the panels.  Rows of the result above the first column k0 with a
+// non-finite entry do not depend on R2's rows from k0 on, but a panel's products
+// run over whole row blocks, and the zeros that it has there would not hide
+// a NaN.  Column k0 as a NaN says the same without those rows.
+template <typename T, int NC>
+__device__ __forceinline__ void isolate_not_finite(Chunk<T, MergeRows<T, NC>::RB, Slots<NC>::NS>& c)
+{
+    constexpr int RB = MergeRows<T, NC>::RB, NS = Slots<NC>::NS;
+    const int lane = lane_id();
+    const int q = c.q(lane), p = c.p(lane);
+    int k0 = NC;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(!(c.get(r, s) * T(0) == T(0)));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = 4 * (s + merge_first<T>(r)) + j;
+                if ((m & ((uint64_t)0x1111111111111111 << j)) != 0 && k < k0) k0 = k;
+            }
+        }
+    if (k0 == 0) return;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const T t = 4 * (s + merge_first<T>(r)) + q == k0 ? T(__builtin_nan("")) : (T)c.get(r, s);
+            c.put(r, s, 16 * r + p < k0 ? t : T(0));
+        }
+}
+
 // Tree node id: Rs := qr([Rs; R2]), Rs packed in LDS, R2 in c as well as, packed,
 // at R2.  Panels that Rs calls close are done one column at a time.  In the narrow
 // widths, where four panels hold little arithmetic, the whole merge is then done
@@ -442,8 +486,9 @@ __device__ __forceinline__ void merge_node(const Args& a, int id, const T* R2,
     T* Vn = WQ ? a.qs.Vn + (int64_t)id * Tri<NC>::kSize : nullptr;
     T* tau = WQ ? a.qs.tau_node + (int64_t)id * NC : nullptr;
     const uint64_t columns = close_columns<T, NC>(Rs);
+    const bool bad = not_finite(c);
     unsigned close = 0;
-    if (columns != 0) [[unlikely]] {
+    if (columns != 0 || bad) [[unlikely]] {
         if constexpr (NC <= kColumnMerge) {
             T v[NC];
             triangle_column<T, NC>(R2, v);
@@ -457,6 +502,7 @@ __device__ __forceinline__ void merge_node(const Args& a, int id, const T* R2,
             }
             return;
         }
+        if (bad) isolate_not_finite<T, NC>(c);
 #pragma unroll
         for (int P = 0; P < Slots<NC>::NS; ++P) close |= (columns >> 4 * P & 15) != 0 ? 1u << P : 0;
     }

@@ -566,15 +566,15 @@ __device__ __forceinline__ bool panel_columns(Chunk<T, RB, 1>& c, T* row0, int r
             calm = calm && (__builtin_amdgcn_ballot_w64(!(grow <= T(kMaxGrowth) * S)) & 1) == 0 &&
                    (normal || __builtin_amdgcn_ballot_w64(sigma2 != T(0) || alpha != T(0)) == 0);
             const T s = h.sy * h.q;
-            const T f = k > j ? h.sy * fmadd(s, d, rk) : T(0);
+            const T f = h.sy * fmadd(s, d, rk);
 #pragma unroll
             for (int r = 0; r < RA; ++r) {
                 T own = c.get(r, 0);
                 asm volatile("" : "+v"(own));
                 const T x = dpp_mov<0x00>(own);
-                c.put(r, 0, fmadd(-f, x, own));
+                c.put(r, 0, k > j ? fmadd(-f, x, own) : own);    // (0 times a NaN is one)
             }
-            grow = fmadd(f, f * sigma2, grow);
+            grow = k > j ? fmadd(f, f * sigma2, grow) : grow;
             if (lane < 4 && k >= j && k < row) Rj[k] = k == j ? h.beta : fmadd(-h.z, rk, -h.sy * d);
             if (lane == 0) {
                 work[4 * j] = h.z;

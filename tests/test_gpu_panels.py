@@ -158,6 +158,33 @@ def test_close_columns_in_some_chunks(n, leaf_rows, dt):
 
 
 @pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n,col", [(8, 5), (12, 1), (20, 7), (50, 0), (50, 5), (50, 24), (64, 63)])
+@pytest.mark.parametrize("leaf_rows", [1024, 128])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_not_finite_column(n, col, leaf_rows, dt, value):
+    """A NaN or an infinity in a column stays out of the rows of R before it,
+    but for its own column, wherever in A it is; everything after is not finite,
+    the diagonal (of which the contract says nothing) left aside."""
+    npdt, _, _ = DT[dt]
+    rows, cols = np.triu_indices(n)
+    above = (rows < col) & (cols != col)
+    for row in (3, 400, 899):
+        A = inputs.uniform(900, n, 31, npdt)
+        B = A.copy()
+        A[:, col] = 0
+        B[row, col] = value
+        h = tsqr.handle(0)
+        tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, leaf_rows)
+        try:
+            R = tsqr.geqr_r(to_dev(B)).cpu().numpy()[rows, cols]
+        finally:
+            tsqr.tsqr_set_option(h, tsqr.TSQR_OPT_LEAF_ROWS, 0)
+        ref = oracle.r_factor(np.asfortranarray(A.astype(np.float64)))[rows, cols]
+        assert np.all(np.abs(R[above] - ref[above]) < (1e-10 if dt == "f64" else 1e-3))
+        assert not np.any(np.isfinite(R[(rows >= col) & (cols > rows)]))
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
 @pytest.mark.parametrize("sizes", [(30000,), (8192, 8193, 64, 20000, 1), (70000, 300)])
 def test_batch_leaves_fill_the_device(sizes, dt):
     npdt, gram, _ = DT[dt]
