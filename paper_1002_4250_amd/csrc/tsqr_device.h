@@ -562,7 +562,6 @@ template <typename T, int NC, int RPL, bool WQ = false, typename TIn = T>
 __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int leaf, T* Rs, T* red)
 {
     constexpr int CH = 16 * RPL;                  // rows per chunk
-    constexpr int NT = Tri<NC>::kSize;
     constexpr int NS = Slots<NC>::NS;
     const int lane = lane_id();
     // column 4s + q and row p + 16 r of register (r, s)
@@ -623,6 +622,46 @@ __device__ __forceinline__ void leaf_phase(const LeafTreeArgs<T, TIn>& a, int le
     if (a.stamps && lane == 0) {
         a.stamps[4 * leaf] = t_start;
         a.stamps[4 * leaf + 1] = (uint64_t)wall_clock64();
+    }
+}
+
+// The root, reached by leaf `leaf`'s wavefront at tree level `level`: positive
+// diagonal, +0 below it, leading n-by-n block only (lane i writes row i, eight
+// columns in flight).
+template <typename T, int NC, bool WQ = false, typename TIn = T>
+__device__ __forceinline__ void finish_root(const LeafTreeArgs<T, TIn>& a, int leaf, int level, const T* Rs)
+{
+    const int lane = lane_id();
+    const int n = a.n;
+    {
+        const int i = lane < n ? lane : 0;
+        const T* row = Rs + Tri<NC>::off(i) - i;
+        const bool flip = __builtin_signbit(row[i]);
+        for (int k0 = 0; k0 < n; k0 += 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = row[k0 + u];      // past the row's end: inside the padding
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u;
+                const T x = k < i ? T(0) : (flip ? -v[u] : v[u]);
+                if (lane < n && k < n) a.R[i + (int64_t)k * a.ldr] = x;
+            }
+        }
+    }
+    if (a.stamps && lane == 0) {
+        a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
+        a.stamps[4 * leaf + 3] = (uint64_t)(100 + level);
+    }
+    if constexpr (WQ) {
+        // R = D R_raw with D the diagonal of signs, so Q = Q_raw D: the tree
+        // pass starts from [D; 0] (identity past column n)
+        for (int idx = lane; idx < NC * NC; idx += kWave) {
+            const int i = idx % NC, k = idx / NC;
+            T d = T(0);
+            if (i == k) d = (k < n && __builtin_signbit(Rs[Tri<NC>::off(k)])) ? T(-1) : T(1);
+            a.qs.qblk[idx] = d;
+        }
     }
 }
 
@@ -687,46 +726,7 @@ __device__ __forceinline__ void tree_phase(const LeafTreeArgs<T, TIn>& a, int le
         if (!root) triangle_to_global<T, NC>(Rs, a.tri + (int64_t)node * NT);
     }
 
-    // root: positive diagonal, +0 below it, leading n-by-n block only
-    // (lane i holds row i, eight columns in flight)
-    const int n = a.n;
-    {
-        const int i = lane < n ? lane : 0;
-        const T* row = Rs + Tri<NC>::off(i) - i;
-        const bool flip = __builtin_signbit(row[i]);
-        for (int k0 = 0; k0 < n; k0 += 8) {
-            T v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = row[k0 + u];      // past the row's end: inside the padding
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u;
-                const T x = k < i ? T(0) : (flip ? -v[u] : v[u]);
-                if (lane < n && k < n) a.R[i + (int64_t)k * a.ldr] = x;
-            }
-        }
-    }
-    if (a.stamps && lane == 0) {
-        a.stamps[4 * leaf + 2] = (uint64_t)wall_clock64();
-        a.stamps[4 * leaf + 3] = (uint64_t)(100 + level);
-    }
-    if constexpr (WQ) {
-        // R = D R_raw with D the diagonal of signs, so Q = Q_raw D: the tree
-        // pass starts from [D; 0] (identity past column n)
-        for (int idx = lane; idx < NC * NC; idx += kWave) {
-            const int i = idx % NC, k = idx / NC;
-            T d = T(0);
-            if (i == k) d = (k < n && __builtin_signbit(Rs[Tri<NC>::off(k)])) ? T(-1) : T(1);
-            a.qs.qblk[idx] = d;
-        }
-    }
-}
-
-template <typename T, int NC, int RPL, bool WQ = false, typename TIn = T>
-__device__ __forceinline__ void leaf_tree_body(const LeafTreeArgs<T, TIn>& a, int leaf, T* Rs, T* red)
-{
-    leaf_phase<T, NC, RPL, WQ, TIn>(a, leaf, Rs, red);
-    tree_phase<T, NC, WQ, TIn>(a, leaf, leaf, 0, Rs, red);
+    finish_root<T, NC, WQ>(a, leaf, level, Rs);
 }
 
 // Workgroups are dispatched to the 8 XCDs in turn (workgroup g to XCD g mod 8),
@@ -750,12 +750,14 @@ struct LeafWaves {
     static constexpr int kPerSimd = kChunkRegs <= 184 ? 2 : 1;
 };
 
+// A single leaf: no tree
 template <typename T, int NC, int RPL, bool WQ = false>
-__global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_leaf_tree_kernel(LeafTreeArgs<T> a)
+__global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_leaf_kernel(LeafTreeArgs<T> a)
 {
     __shared__ T Rs[Tri<NC>::kPadded];
-    __shared__ __align__(16) T red[PanelLds<T, (RPL > 4 ? RPL : 4)>::kElems];
-    leaf_tree_body<T, NC, RPL, WQ>(a, xcd_local_leaf(blockIdx.x, a.leaves), Rs, red);
+    __shared__ __align__(16) T red[PanelLds<T, RPL>::kElems];
+    leaf_phase<T, NC, RPL, WQ>(a, 0, Rs, red);
+    finish_root<T, NC, WQ>(a, 0, 0, Rs);
 }
 
 // Four leaves per workgroup, one wavefront each (one per SIMD of a compute
@@ -765,10 +767,9 @@ __global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr
 // on a 1024-leaf tree, that global handoff costs 26 us at level 0 and 14 us at
 // level 1, where every wavefront fences at once, against 2-6 us above.  The
 // merges take the same operands in the same order (the lower index on top),
-// so R is bit-identical to tsqr_leaf_tree_kernel's.  The wavefronts of the last
-// workgroup past the last leaf only keep the barriers; with at most four leaves
-// no tree counter is touched.  Groups are numbered XCD-locally as single leaves
-// are.
+// so R is bit-identical to that of one leaf per workgroup, as the batched kernel
+// has it.  The wavefronts of the last workgroup past the last leaf only keep
+// the barriers; with at most four leaves no tree counter is touched.
 template <typename T, int NC, int RPL, bool WQ = false>
 __global__ void __launch_bounds__(4 * kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr_leaf_tree4_kernel(LeafTreeArgs<T> a)
 {
@@ -832,7 +833,8 @@ __global__ void __launch_bounds__(kWave, (LeafWaves<T, NC, RPL>::kPerSimd)) tsqr
     a.R = b.R + (int64_t)t.inst * b.ldr * b.n;
     a.ldr = b.ldr;
     a.qs = QStore<T>{};
-    leaf_tree_body<T, NC, RPL, false, TIn>(a, t.leaf, Rs, red);
+    leaf_phase<T, NC, RPL, false, TIn>(a, t.leaf, Rs, red);
+    tree_phase<T, NC, false, TIn>(a, t.leaf, t.leaf, 0, Rs, red);
     if (b.stamps && threadIdx.x == 0) {
         b.stamps[2 * blockIdx.x] = t_start;
         b.stamps[2 * blockIdx.x + 1] = (uint64_t)wall_clock64();

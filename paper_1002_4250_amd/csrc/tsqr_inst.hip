@@ -26,7 +26,7 @@ hipError_t TSQR_LEAF_FN2(TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)(const LeafT
         hipLaunchKernelGGL((dev::tsqr_leaf_tree4_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL>),
                            dim3((a.leaves + 3) / 4), dim3(4 * dev::kWave), 0, s, a);
     else
-        hipLaunchKernelGGL((dev::tsqr_leaf_tree_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL>), dim3(a.leaves),
+        hipLaunchKernelGGL((dev::tsqr_leaf_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL>), dim3(1),
                            dim3(dev::kWave), 0, s, a);
     return hipGetLastError();
 }
@@ -39,10 +39,10 @@ int TSQR_OCC_FN2(TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)()
     if (cached < 0) {
         int n = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &n, dev::tsqr_leaf_tree_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL>, dev::kWave, 0) !=
+                &n, dev::tsqr_leaf_tree4_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL>, 4 * dev::kWave, 0) !=
             hipSuccess)
             return 0;
-        cached = n;
+        cached = 4 * n;
     }
     return cached;
 }
@@ -82,8 +82,8 @@ hipError_t TSQR_QR_FN2(qr_leaf_tree, TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)
         hipLaunchKernelGGL((dev::tsqr_leaf_tree4_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL, true>),
                            dim3((a.leaves + 3) / 4), dim3(4 * dev::kWave), 0, s, a);
     else
-        hipLaunchKernelGGL((dev::tsqr_leaf_tree_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL, true>),
-                           dim3(a.leaves), dim3(dev::kWave), 0, s, a);
+        hipLaunchKernelGGL((dev::tsqr_leaf_kernel<TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL, true>), dim3(1),
+                           dim3(dev::kWave), 0, s, a);
     return hipGetLastError();
 }
 hipError_t TSQR_QR_FN2(q_tree, TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)(const LeafTreeArgs<TSQR_INST_TAG>& a,
