@@ -33,6 +33,7 @@ DEFAULT_TABLE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning
 DTYPES = {"f64": tsqr.TSQR_F64, "f32": tsqr.TSQR_F32}
 M_BUCKETS = [1 << 12, 1 << 14, 1 << 16, 1 << 18, 1 << 20, 1 << 22]
 WAVES_PER_CU = [1, 2, 4, 8, 16]
+# (43 chunks of 12 rows per lane: eight leaves to 65536 rows)
 BATCH_LEAF_CHUNKS = [16, 32, 43, 64, 128, 256]
 # No candidate longer than this (plus a chunk): with longer leaves a batch of
 # 2^24 rows does not give every resident wavefront a leaf.  256 of 65536 x 50
