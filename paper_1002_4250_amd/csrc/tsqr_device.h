@@ -29,7 +29,7 @@
 // them the four dependent reflectors.  A chunk of 128 rows at n = 50 in FP64
 // takes 21 us on its own (about 3900 cycles a panel), a merge of two triangles
 // 16 us.  One column at a time on the vector units the chunk took 37 us, and
-// 2^22 x 50 1437 us per call in FP64 and 767 us in FP32; now 898 and 625 us.
+// 2^22 x 50 1437 us per call in FP64 and 767 us in FP32; now 882 and 607 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -743,11 +743,17 @@ __device__ __forceinline__ int xcd_local_leaf(int g, int P)
 }
 
 // Wavefronts per SIMD the register budget is held to: two where the chunk leaves
-// room for the working set of a panel
+// room for the working set of a panel.  FP64 at 40 columns (160 registers) spilled
+// up to 100 registers at two: at one, with half the leaves, Q and R of 10^6 x 40
+// take 697 us (754 at two), 300000 x 40 with Q^T of ten columns 373 (426), R of 10^6 x
+// 40 260 (271), of 4 10^6 x 40 605 (590).  156 registers (FP32, 50 columns, 12 rows)
+// and FP32 at 64 columns (128) are better at two although the latter spills: R
+// of 20001 x 64 188 us (215 at one), Q and R in FP64 at 32 columns (128) 10^6 x
+// 32 580 (676).
 template <typename T, int NC, int RPL>
 struct LeafWaves {
     static constexpr int kChunkRegs = RPL * Slots<NC>::NS * (int)(sizeof(T) / 4);
-    static constexpr int kPerSimd = kChunkRegs <= 184 ? 2 : 1;
+    static constexpr int kPerSimd = kChunkRegs < 160 ? 2 : 1;
 };
 
 // A single leaf: no tree

@@ -131,8 +131,8 @@ hipError_t TSQR_QR_FN2(qt, TSQR_INST_TAG, TSQR_INST_NC, TSQR_INST_RPL)(const QtA
     // the step's working set, no spills), 64 in FP32, so k = n = 50 takes one
     // pass over the reflectors; a narrower panel takes 8, 4 or 1 slots (32, 16
     // or 4 columns): a pass costs a fixed part (reading the reflectors and
-    // replaying their chain, about 1.1 ms at 2^22 x 50 in FP64) plus about
-    // 0.1 ms per slot
+    // replaying their chain) plus about 0.07 ms per slot (2^22 x 50 in FP64:
+    // 0.57 ms with one slot, 1.43 ms with 13)
     constexpr int KW = sizeof(TSQR_INST_TAG) == 8 ? 13 : 16;
     if (x.k <= 0) return hipSuccess;
     hipError_t e = hipSuccess;

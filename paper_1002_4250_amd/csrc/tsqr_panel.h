@@ -784,7 +784,7 @@ __device__ __forceinline__ void panel_step(Chunk<T, RB, Slots<NC>::NS>& c, T* Rs
         // on a copy of the slot: in FP64 at one wavefront per SIMD the chunk
         // lies in registers that only the matrix instructions reach, and a panel
         // that could change it here would be moved out of them in either case
-        // (2^22 x 50: 935 us, 870 as it is)
+        // (2^22 x 50: 935 us against 870)
         Chunk<T, RB, 1> x = slot_of(c, P);
         const bool calm = panel_columns<T, RA>(x, Rs + Tri<NC>::off(J0), NC - J0, NJ, work, col);
         hard = calm ? hard & ~(1u << P) : hard | 1u << P;
