@@ -338,7 +338,7 @@ int tsqr_apply_qt_f32(tsqr_handle_t handle, int64_t m, int64_t n, int64_t k, con
  * needed it) is refactored by the plain FP64 TSQR path, which reads its FP32
  * storage directly; that decision is taken on the device.  Of this form and the
  * sampled one below only the sampled one is faster than the plain FP64 batch
- * (256 of 65536 x 50: 3.7 ms so, 2.3 ms sampled, 3.1 ms plain FP64): use this one
+ * (256 of 65536 x 50: 3.8 ms so, 2.3 ms sampled, 2.9 ms plain FP64): use this one
  * where A is at hand in FP32 only and no sample is wanted.
  *
  * Create: argument codes -1 handle, -2 batch, -3 m, -4 n, -5 lda, -6 stride_a,
